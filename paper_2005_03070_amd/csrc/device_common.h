@@ -263,13 +263,8 @@ __device__ __forceinline__ int cycle_tolerance(double nu, double nu0, double tau
     } else {
         const double t1 = pow(tau / nu, 1.0 / (double)(ncyc - icyc + 1));
         const double t2 = (nu0 / nu) * pow(tau / nu0, (double)icyc / (double)ncyc);
-        if (t1 <= t2) {
-            rt = t1;
-            branch = 1;
-        } else {
-            rt = t2;
-            branch = 2;
-        }
+        branch = t1 <= t2 ? 1 : 2;
+        rt = branch == 1 ? t1 : t2;
     }
     if (fp32 == 1 && rt < fp32_floor) rt = fp32_floor;
     return branch;
@@ -394,12 +389,21 @@ __device__ __forceinline__ double wave_sum(double v) {
 
 // One data-parallel-primitive move of a double (two 32-bit halves): lane i
 // receives the source lane that CTRL selects; lanes of rows outside ROWMASK
-// receive 0.
+// receive 0.  With every row enabled the quad permutations, rotations and
+// mirrors have a source for every lane, so no zero is written first.
+template <int CTRL, int ROWMASK>
+__device__ __forceinline__ int dpp_move32(int v) {
+    if constexpr (ROWMASK == 0xf)
+        return __builtin_amdgcn_mov_dpp(v, CTRL, 0xf, 0xf, false);
+    else
+        return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWMASK, 0xf, false);
+}
 template <int CTRL, int ROWMASK>
 __device__ __forceinline__ double dpp_move(double v) {
+    static_assert(ROWMASK != 0xf || CTRL < 0x100 || CTRL > 0x11f, "a row shift leaves lanes without a source");
     const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
-    const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)b, CTRL, ROWMASK, 0xf, false);
-    const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, ROWMASK, 0xf, false);
+    const unsigned lo = (unsigned)dpp_move32<CTRL, ROWMASK>((int)(unsigned)b);
+    const unsigned hi = (unsigned)dpp_move32<CTRL, ROWMASK>((int)(unsigned)(b >> 32));
     return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
 }
 

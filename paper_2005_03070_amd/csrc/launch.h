@@ -48,6 +48,12 @@ void launch_step_dim(int inner_f32, int var, int tile_id, const DevProb* probs, 
 // Workgroups per compute unit of the 3-D step kernel (occupancy; 0 if unknown).
 int step_blocks_per_cu(int inner_f32, int var, int tile_id);
 
+// Chip-resident BiCGStab solve of 2-D systems: sets up the states and the
+// exchange regions (and, with args.upload, the descriptors in host memory at
+// probs), then launches teams * args.team workgroups cooperatively.
+hipError_t launch_resident2d(int inner_f32, int var, const ResArgs& args, const DevProb* probs, int teams,
+                             hipStream_t s);
+
 // IDR(s) inner cycles (kernels_idr.hip): what = one of the IDR_* actions,
 // k = the step of the round for IDR_DIR, IDR_ALPHA, IDR_ORTH, IDR_UPD.
 enum : int {

@@ -86,6 +86,10 @@ struct Group {
     int* d_wgprob = nullptr;
     unsigned char* d_actlog = nullptr;  // action log of problem 0 (measurement only)
     unsigned long long* d_ts = nullptr;  // per-launch first start / last end (measurement only)
+    // chip-resident solve (kernels_resident2d.hip): workgroups per team (0:
+    // the step kernel), teams, and the exchange regions
+    int team = 0, teams = 0;
+    ResArgs res;
     std::vector<DevProb> probs;
     std::vector<SolveState> states;
     std::vector<int> wgprob;
@@ -186,6 +190,33 @@ struct ExtWs {
     size_t cap;
 };
 
+// Workgroups per team of the chip-resident solve, or 0 where the step kernel
+// solves the group: BiCGStab on 2-D grids of at most one 64 x 64 tile per
+// compute unit (every workgroup of a team must be resident, one per unit).
+// Up to that size it is faster everywhere: 63^2 (one tile) 14.9 -> 3.1 us per
+// iteration, 1023^2 (256 tiles) 31.8 -> 7.5 us; beyond it the tiles do not fit.
+// With the measurement of single step launches on, the step kernel runs.
+static int resident_team(tgdk_ctx ctx, const std::vector<ProbSpec>& ps, const tgdk_solve_params* prm) {
+    if (ps[0].op->dim != 2 || prm->method != TGDK_BICGSTAB_PROJ || ctx->time_which) return 0;
+    long long team = 0;
+    for (const auto& p : ps) {
+        const long long tx = (p.op->n[0] + RES_TILE - 1) / RES_TILE, ty = (p.op->n[1] + RES_TILE - 1) / RES_TILE;
+        team = std::max(team, tx * ty);
+    }
+    return team <= std::min(ctx->num_cus, 256) ? (int)team : 0;
+}
+
+static void set_space(DevProb& P, tgdk_defl d) {
+    if (!d) return;
+    P.V = d->V;
+    P.Vl = d->W ? d->W : d->V;
+    P.ldv = d->n;
+    P.lu = d->d_lu;
+    P.piv = d->d_piv;
+    P.hinv = d->d_hinv;
+    P.vtype = d->store == TGDK_F32 ? 1 : 0;
+}
+
 // Fills the device-side group description and workspaces (allocated in the
 // context's grow-only buffer, or laid out in ext).
 static int build_group(tgdk_ctx ctx, const std::vector<ProbSpec>& ps, const tgdk_solve_params* prm, Group& g,
@@ -230,6 +261,7 @@ static int build_group(tgdk_ctx ctx, const std::vector<ProbSpec>& ps, const tgdk
     // phases at n_x = 255); x, b and V keep the caller's pitch n_x.  The
     // other drivers' kernels and the 2-D tile paths assume pitch n_x.
     const bool padded = g.dim == 3 && prm->method == TGDK_BICGSTAB_PROJ;
+    g.team = resident_team(ctx, ps, prm);
     std::vector<size_t> nstore(g.nprob);  // elements per stored vector
     for (int j = 0; j < g.nprob; ++j) {
         const tgdk_op op = ps[j].op;
@@ -286,6 +318,21 @@ static int build_group(tgdk_ctx ctx, const std::vector<ProbSpec>& ps, const tgdk
     if (stamps) off += align256(sizeof(unsigned long long) * 2 * NTSLOG * (size_t)g.probs[0].nwg);
     int rc;
     char* base;
+    // the resident solve's workspace: descriptors, states, exchange regions
+    size_t res_xch = 0;
+    if (g.team) {
+        g.teams = std::max(1, std::min(g.nprob, std::min(ctx->num_cus, 256) / g.team));
+        g.res.kmax = 0;
+        for (const DevProb& P : g.probs) g.res.kmax = std::max(g.res.kmax, P.k);
+        g.res.xstride = res_exchange_words(g.team, g.res.kmax);
+        res_xch = align256(off_counters + 256);
+        const size_t need = res_xch + align256((size_t)g.res.xstride * g.teams * 8);
+        // (in a caller's workspace both have to fit, so that the step
+        // kernel's decides what is refused; a few KB of vectors can be less
+        // than the regions)
+        if (ext && need > ext->cap && off <= ext->cap) g.team = 0;
+        if (!ext) off = need;
+    }
     if (ext) {
         if (off > ext->cap) {
             char msg[160];
@@ -308,6 +355,41 @@ static int build_group(tgdk_ctx ctx, const std::vector<ProbSpec>& ps, const tgdk
     g.d_ts = stamps ? (unsigned long long*)(base + off_ts) : nullptr;
     unsigned* counters = (unsigned*)(base + off_counters);
     g.mirror = ctx->mirror;
+    if (g.team) {
+        ResArgs& a = g.res;
+        a.probs = g.d_probs;
+        a.nprob = g.nprob;
+        a.team = g.team;
+        a.ctl = counters;
+        a.xch = base + res_xch;
+        a.states = g.d_states;
+        a.upload = g.nprob <= RES_ARGPROBS;
+        ResInit& in = a.init;
+        memset(&in, 0, sizeof(in));
+        in.rtol = prm->rtol;
+        in.fp32_floor = prm->fp32_floor > 0 ? prm->fp32_floor : 1e-4;
+        in.nu0_in = prm->nu0;
+        in.method = METHOD_BICGSTAB;
+        in.ncyc = prm->ncyc;
+        in.max_extra = prm->max_extra_cycles >= 0 ? prm->max_extra_cycles : prm->ncyc;
+        in.maxit = prm->maxit_cycle > 0 ? prm->maxit_cycle : 100000;
+        in.precision = g.inner_f32;
+        in.icyc0 = prm->icyc0;
+        in.maxcyc_call = prm->max_cycles_call;
+        in.zero_start = !prm->x0_given;
+        for (int j = 0; j < g.nprob; ++j) {
+            DevProb& P = g.probs[j];
+            P.b = ps[j].b;
+            P.x = ps[j].x;
+            P.st = g.d_states + j;
+            set_space(P, ps[j].defl);
+        }
+        if (!a.upload)
+            TGDK_HIP(hipMemcpyAsync(g.d_probs, g.probs.data(), sizeof(DevProb) * g.nprob, hipMemcpyHostToDevice,
+                                    ctx->stream));
+        g.states.assign(g.nprob, SolveState());
+        return TGDK_OK;
+    }
     g.states.assign(g.nprob, SolveState());
     std::vector<int>& wgprob = g.wgprob;
     wgprob.assign((size_t)wgs, 0);
@@ -338,15 +420,7 @@ static int build_group(tgdk_ctx ctx, const std::vector<ProbSpec>& ps, const tgdk
         P.t = vecs[i++];
         P.e = vecs[i++];
         if (g.dim == 3 && P.k > 0) P.w = (double*)v;
-        if (ps[j].defl) {
-            P.V = ps[j].defl->V;
-            P.Vl = ps[j].defl->W ? ps[j].defl->W : ps[j].defl->V;
-            P.ldv = ps[j].defl->n;
-            P.lu = ps[j].defl->d_lu;
-            P.piv = ps[j].defl->d_piv;
-            P.hinv = ps[j].defl->d_hinv;
-            P.vtype = ps[j].defl->store == TGDK_F32 ? 1 : 0;
-        }
+        set_space(P, ps[j].defl);
         P.st = g.d_states + j;
         P.partial = (double*)(base + off_part[j]);
         P.actlog = j == 0 ? g.d_actlog : nullptr;
@@ -456,7 +530,7 @@ static int finish_group(Group& g, const std::vector<ProbSpec>& ps, tgdk_solve_re
                         const std::vector<long long>* extra_inner, const std::vector<int>* cycle_steps = nullptr,
                         int idr_s = 0) {
     hipStream_t s = g.ctx->stream;
-    launch(g, K_RESIDUAL, 2);
+    if (!g.team) launch(g, K_RESIDUAL, 2);  // (the resident solve ends with the true residual)
     TGDK_HIP(hipGetLastError());
     TGDK_HIP(hipMemcpyAsync(g.states.data(), g.d_states, sizeof(SolveState) * g.nprob, hipMemcpyDeviceToHost, s));
     TGDK_HIP(hipStreamSynchronize(s));
@@ -533,6 +607,23 @@ static int predict_steps(const Mirror& m, Predict& pr) {
     return 2 * rem + 3 + 2 * pr.len + 3;
 }
 
+// The chip-resident solve: one launch runs every system of the group to its
+// end; the host waits for it.
+static int resident_group(Group& g, const std::vector<ProbSpec>& ps, tgdk_solve_report* reps,
+                          std::chrono::steady_clock::time_point t0) {
+    tgdk_ctx ctx = g.ctx;
+    hipStream_t s = ctx->stream;
+    TGDK_HIP(launch_resident2d(g.inner_f32, g.var, g.res, g.probs.data(), g.teams, s));
+    TGDK_HIP(hipEventRecord(ctx->events[0], s));
+    int rc = wait_event(ctx->events[0]);
+    if (rc) return rc;
+    const double secs = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
+    unsigned ctl[2] = {0, 0};
+    TGDK_HIP(hipMemcpyAsync(ctl, g.res.ctl, sizeof(ctl), hipMemcpyDeviceToHost, s));
+    rc = finish_group(g, ps, reps, secs, nullptr);
+    return ctl[1] ? fail(TGDK_E_HIP, "the resident solve stopped making progress") : rc;
+}
+
 // BiCGStab(ncyc)-Proj(k) over a group: step launches only.  At most two
 // batches are outstanding; when the older one completes, the host reads the
 // status mirror and enqueues as many steps as the slowest running problem is
@@ -545,6 +636,7 @@ static int bicgstab_group(tgdk_ctx ctx, const std::vector<ProbSpec>& ps, const t
     int rc = build_group(ctx, ps, prm, g, ext);
     if (rc) return rc;
     if (!ext && (rc = ensure_events(ctx, 2))) return rc;
+    if (g.team) return resident_group(g, ps, reps, t0);
     hipStream_t s = ctx->stream;
     const int S_MAX = 24;  // largest batch of steps enqueued at once
     const long long max_cycles = prm->ncyc + (prm->max_extra_cycles >= 0 ? prm->max_extra_cycles : prm->ncyc) + 2;

@@ -64,8 +64,7 @@ __device__ __forceinline__ T pick2(const T (&a)[2], int i) {
 // Start of an inner cycle from a residual of norm nu: its tolerance
 // (Sec. 4.1 step 3 b, cycle_tolerance) and fresh BiCGStab scalars; returns
 // the criterion taken (1, 2 or 3).
-__device__ __forceinline__ int cycle_start(StepHot& N, const SolveState* st, double nu, double rho0, double& rt) {
-    const int branch = cycle_tolerance(nu, N.nu0, N.tau, N.icyc, st->ncyc, st->precision, st->fp32_floor, rt);
+__device__ __forceinline__ void cycle_reset(StepHot& N, double nu, double rho0, double rt) {
     N.target2 = (rt * nu) * (rt * nu);
     N.rho = rho0;
     N.rho_old = 1.0;
@@ -74,14 +73,18 @@ __device__ __forceinline__ int cycle_start(StepHot& N, const SolveState* st, dou
     N.iter = 0;
     N.inner_state = IN_RUNNING;
     N.upd_any = 0;
+}
+__device__ __forceinline__ int cycle_start(StepHot& N, const SolveState* st, double nu, double rho0, double& rt) {
+    const int branch = cycle_tolerance(nu, N.nu0, N.tau, N.icyc, st->ncyc, st->precision, st->fp32_floor, rt);
+    cycle_reset(N, nu, rho0, rt);
     return branch;
 }
 
 // Tests on the true residual nu = ||b - A x|| at a cycle boundary (or at the
 // start of the solve): Sec. 4.1 steps 1 and 4; the cycle count goes up if the
-// solve continues.
-__device__ __forceinline__ void boundary_tests(const StepHot& H, StepHot& N, const SolveState* st, double nu,
-                                               double bb) {
+// solve continues.  st: the solve's parameters (SolveState, or ResInit).
+template <class ST>
+__device__ __forceinline__ void boundary_tests(const StepHot& H, StepHot& N, const ST* st, double nu, double bb) {
     if (H.first) {
         // a resumed solve keeps the schedule of its first call: nu0 and
         // tau = rtol min(||b||, nu0) come from there, and it starts at cycle

@@ -154,6 +154,38 @@ struct DevProb {
     Mirror* mirror;
 };
 
+// Chip-resident 2-D solve (kernels_resident2d.hip): teams of `team`
+// workgroups, one per RES_TILE x RES_TILE tile, take systems from a queue.
+constexpr int RES_TILE = 64;
+constexpr int RES_NSUM = 5;   // most sums of one exchange
+constexpr int RES_COPIES = 16;  // copies of an exchange's totals (read by different workgroups)
+constexpr int RES_ARGPROBS = 4;  // descriptors passed in the set-up kernel's arguments
+// A solve's parameters, the same for every system (names as in SolveState).
+struct ResInit {
+    double rtol, fp32_floor, nu0_in;
+    int method, ncyc, max_extra, maxit, precision, icyc0, maxcyc_call;
+    int zero_start;          // x starts at 0 (its contents are not read)
+};
+struct ResArgs {
+    DevProb* probs;
+    int nprob, team, kmax;
+    int upload;              // the set-up kernel stores the descriptors of its arguments
+    long long xstride;       // 64-bit words of a team's exchange region
+    void* xch;               // the teams' exchange regions
+    unsigned* ctl;           // [0] next system, [1] raised when a wait has timed out
+    SolveState* states;
+    ResInit init;
+};
+struct ResProbs {
+    DevProb p[RES_ARGPROBS];
+};
+// Exchange region of a team: sums, totals and tile edges (three buffers
+// each), the column partials and values of c = V^T r.
+inline long long res_exchange_words(int team, int kmax) {
+    const long long tp = (team + 63) / 64 * 64;
+    return 3 * RES_NSUM * tp + 3 * RES_COPIES * 8 + 3LL * team * 4 * RES_TILE + kmax * (tp + 1) + 15;
+}
+
 constexpr int NSLOTLOG = 1 << 15;
 constexpr int NTSLOG = 1 << 12;
 
