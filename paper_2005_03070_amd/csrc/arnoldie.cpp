@@ -189,7 +189,7 @@ extern "C" int tgdk_defl_improve(tgdk_defl in, const tgdk_arnoldie_params* prm, 
     double* base = nullptr;
     const size_t nd = vec * (2 * (size_t)cq + 4 * (size_t)cy + 1) + 64 * 64 + (size_t)cq * cy + (size_t)cy * cy +
                       4 * (size_t)cq + 8;
-    if (hipMalloc((void**)&base, nd * sizeof(double)) != hipSuccess)
+    if (pool_alloc(ctx, &base, nd))
         return fail(TGDK_E_NOMEM, "Arnoldi-E workspace allocation failed");
     Work w;
     w.ctx = ctx;
@@ -212,7 +212,7 @@ extern "C" int tgdk_defl_improve(tgdk_defl in, const tgdk_arnoldie_params* prm, 
     double* dsc = p;  // [0]: ||z||^2 before, [1]: ||z|| after
     auto done = [&](int code) {
         (void)hipStreamSynchronize(s);
-        (void)hipFree(base);
+        ctx->pool.put(base);
         return code;
     };
     // the partial sums of both the Gram-Schmidt and the 64 x 64 Gram kernels,
@@ -303,11 +303,11 @@ extern "C" int tgdk_defl_improve(tgdk_defl in, const tgdk_arnoldie_params* prm, 
     // the improved space over an orthonormal basis of the kept span
     const int kk = K.kk;
     double* V64 = nullptr;
-    if (hipMalloc((void**)&V64, sizeof(double) * vec * kk) != hipSuccess)
+    if (pool_alloc(ctx, &V64, vec * kk))
         return done(fail(TGDK_E_NOMEM, "Arnoldi-E output allocation failed"));
     TGDK_HIP(hipMemcpyAsync(V64, w.Y, sizeof(double) * vec * kk, hipMemcpyDeviceToDevice, s));
     if ((rc = cholqr2(ctx, V64, n, kk)) || (rc = defl_finish(op, tr, V64, kk, store_dtype, out, TGDK_PROJ_GALERKIN))) {
-        (void)hipFree(V64);
+        ctx->pool.put(V64);
         return done(rc);
     }
     if (rep) {

@@ -43,6 +43,69 @@ void DevBuf::release() {
     cap = 0;
 }
 
+void DevPool::trim(size_t room) {
+    for (size_t i = 0; i < idle.size();) {  // oldest first
+        if (now - idle[i].stamp <= POOL_AGE && held + room <= POOL_BYTES) {
+            ++i;
+            continue;
+        }
+        held -= idle[i].bytes;
+        (void)hipFree(idle[i].p);
+        idle.erase(idle.begin() + i);
+    }
+}
+
+void* DevPool::get(size_t bytes) {
+    std::lock_guard<std::mutex> lock(mutex);
+    ++now;
+    size_t best = idle.size();
+    for (size_t i = 0; i < idle.size(); ++i)
+        if (idle[i].bytes >= bytes && idle[i].bytes - bytes <= idle[i].bytes / 8 &&
+            (best == idle.size() || idle[i].bytes < idle[best].bytes))
+            best = i;
+    void* p = nullptr;
+    if (best < idle.size()) {
+        p = idle[best].p;
+        taken[p] = idle[best].bytes;
+        held -= idle[best].bytes;
+        idle.erase(idle.begin() + best);
+        trim(0);
+        return p;
+    }
+    trim(0);
+    if (hipMalloc(&p, bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        for (const Block& b : idle) (void)hipFree(b.p);
+        idle.clear();
+        held = 0;
+        if (hipMalloc(&p, bytes) != hipSuccess) return nullptr;
+    }
+    taken[p] = bytes;
+    return p;
+}
+
+void DevPool::put(void* p) {
+    if (!p) return;
+    std::lock_guard<std::mutex> lock(mutex);
+    const auto it = taken.find(p);
+    const size_t bytes = it == taken.end() ? POOL_BYTES + 1 : it->second;
+    if (it != taken.end()) taken.erase(it);
+    if (bytes > POOL_BYTES) {
+        (void)hipFree(p);
+        return;
+    }
+    trim(bytes);
+    idle.push_back({p, bytes, now});
+    held += bytes;
+}
+
+void DevPool::flush() {
+    std::lock_guard<std::mutex> lock(mutex);
+    for (const Block& b : idle) (void)hipFree(b.p);
+    idle.clear();
+    held = 0;
+}
+
 DevOp make_devop(const tgdk_op_s* op, int transpose) {
     DevOp d;
     memset(&d, 0, sizeof(d));
@@ -111,26 +174,16 @@ int op_apply_internal(tgdk_op op, int transpose, int dtype, const void* x, void*
 int cholqr2(tgdk_ctx ctx, double* W, long long n, int k) {
     if (k < 1 || k > MAXK) return fail(TGDK_E_INVALID, "deflation spaces hold 1 to 256 vectors");
     hipStream_t s = ctx->stream;
-    double* tmp = nullptr;
-    double* dY = nullptr;
-    double* dG = nullptr;
-    int rc = dev_alloc(&tmp, (size_t)n * k);
-    if (rc) return rc;
-    if ((rc = dev_alloc(&dY, (size_t)k * k))) {
-        (void)hipFree(tmp);
-        return rc;
-    }
-    if ((rc = dev_alloc(&dG, (size_t)k * k))) {
-        (void)hipFree(tmp);
-        (void)hipFree(dY);
-        return rc;
-    }
+    double *tmp = nullptr, *dY = nullptr, *dG = nullptr;
+    int rc;
+    if (!(rc = pool_alloc(ctx, &tmp, (size_t)n * k)) && !(rc = pool_alloc(ctx, &dY, (size_t)k * k)))
+        rc = pool_alloc(ctx, &dG, (size_t)k * k);
     std::vector<double> G((size_t)k * k), Rinv((size_t)k * k), Y((size_t)k * k);
-    rc = TGDK_OK;
     for (int pass = 0; pass < 2 && rc == TGDK_OK; ++pass) {
+        double *in = pass ? tmp : W, *out = pass ? W : tmp;  // W R_1^{-1} in tmp, the result back in W
         const size_t need = gram_partial_bytes(n, k, k);
         if ((rc = ctx->partial.ensure(need))) break;
-        launch_gram(W, 0, n, k, W, 0, n, k, n, dG, (double*)ctx->partial.p, ctx->counters, s);
+        launch_gram(in, 0, n, k, in, 0, n, k, n, dG, (double*)ctx->partial.p, ctx->counters, s);
         if (hipMemcpyAsync(G.data(), dG, G.size() * sizeof(double), hipMemcpyDeviceToHost, s) != hipSuccess ||
             hipStreamSynchronize(s) != hipSuccess) {
             rc = fail(TGDK_E_HIP, "Gram copy failed");
@@ -147,16 +200,12 @@ int cholqr2(tgdk_ctx ctx, double* W, long long n, int k) {
             rc = fail(TGDK_E_HIP, "upload failed");
             break;
         }
-        launch_vmul(W, n, k, dY, k, tmp, n, n, s);
-        if (hipMemcpyAsync(W, tmp, (size_t)n * k * sizeof(double), hipMemcpyDeviceToDevice, s) != hipSuccess) {
-            rc = fail(TGDK_E_HIP, "copy failed");
-            break;
-        }
+        launch_vmul(in, n, k, dY, k, out, n, n, s);
     }
     if (hipStreamSynchronize(s) != hipSuccess && rc == TGDK_OK) rc = fail(TGDK_E_HIP, "cholqr2 failed");
-    (void)hipFree(tmp);
-    (void)hipFree(dY);
-    (void)hipFree(dG);
+    ctx->pool.put(tmp);
+    ctx->pool.put(dY);
+    ctx->pool.put(dG);
     return rc;
 }
 
@@ -173,15 +222,20 @@ static int defl_factor(tgdk_defl d, const char* singular_msg) {
         col[j] = 1.0;
         lu_solve(k, d->LU.data(), d->piv.data(), col);
     }
+    tgdk_ctx ctx = d->ctx;
+    hipStream_t s = ctx->stream;
     int rc;
-    if ((rc = dev_alloc(&d->d_lu, (size_t)k * k)) || (rc = dev_alloc(&d->d_piv, (size_t)k)) ||
-        (rc = dev_alloc(&d->d_hinv, (size_t)k * k)) ||
-        hipMemcpy(d->d_lu, d->LU.data(), (size_t)k * k * sizeof(double), hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(d->d_piv, d->piv.data(), (size_t)k * sizeof(int), hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(d->d_hinv, hinv.data(), (size_t)k * k * sizeof(double), hipMemcpyHostToDevice) != hipSuccess) {
-        if (d->d_lu) (void)hipFree(d->d_lu);
-        if (d->d_piv) (void)hipFree(d->d_piv);
-        if (d->d_hinv) (void)hipFree(d->d_hinv);
+    if ((rc = pool_alloc(ctx, &d->d_lu, (size_t)k * k)) || (rc = pool_alloc(ctx, &d->d_piv, (size_t)k)) ||
+        (rc = pool_alloc(ctx, &d->d_hinv, (size_t)k * k)) ||
+        hipMemcpyAsync(d->d_lu, d->LU.data(), (size_t)k * k * sizeof(double), hipMemcpyHostToDevice, s) !=
+            hipSuccess ||
+        hipMemcpyAsync(d->d_piv, d->piv.data(), (size_t)k * sizeof(int), hipMemcpyHostToDevice, s) != hipSuccess ||
+        hipMemcpyAsync(d->d_hinv, hinv.data(), (size_t)k * k * sizeof(double), hipMemcpyHostToDevice, s) !=
+            hipSuccess ||
+        hipStreamSynchronize(s) != hipSuccess) {
+        ctx->pool.put(d->d_lu);
+        ctx->pool.put(d->d_piv);
+        ctx->pool.put(d->d_hinv);
         d->d_lu = d->d_hinv = nullptr;
         d->d_piv = nullptr;
         return rc ? rc : fail(TGDK_E_HIP, "upload of LU failed");
@@ -197,19 +251,19 @@ int defl_finish(tgdk_op op, int transpose, double* V64, int k, int store, tgdk_d
     double* AV = nullptr;
     int rc = TGDK_OK;
     if (store == TGDK_F32) {
-        if ((rc = dev_alloc(&V32, (size_t)n * k))) return rc;
+        if ((rc = pool_alloc(ctx, &V32, (size_t)n * k))) return rc;
         launch_to_f32(V64, V32, (long long)n * k, s);
         launch_to_f64(V32, V64, (long long)n * k, s);  // H is formed from the rounded basis
     }
-    if ((rc = dev_alloc(&AV, (size_t)n * k))) {
-        if (V32) (void)hipFree(V32);
+    if ((rc = pool_alloc(ctx, &AV, (size_t)n * k))) {
+        if (V32) ctx->pool.put(V32);
         return rc;
     }
     rc = op_apply_internal(op, transpose, TGDK_F64, V64, AV, k);
     const bool minres = projection == TGDK_PROJ_MINRES;
     float* W32 = nullptr;  // MinRes, float32 storage: the stored A V
     if (!rc && minres && store == TGDK_F32) {
-        rc = dev_alloc(&W32, (size_t)n * k);
+        rc = pool_alloc(ctx, &W32, (size_t)n * k);
         if (!rc) {
             launch_to_f32(AV, W32, (long long)n * k, s);
             launch_to_f64(W32, AV, (long long)n * k, s);  // H is formed from the rounded W
@@ -217,7 +271,7 @@ int defl_finish(tgdk_op op, int transpose, double* V64, int k, int store, tgdk_d
     }
     std::vector<double> H((size_t)k * k);
     double* dG = nullptr;
-    if (!rc) rc = dev_alloc(&dG, (size_t)k * k);
+    if (!rc) rc = pool_alloc(ctx, &dG, (size_t)k * k);
     if (!rc) rc = ctx->partial.ensure(gram_partial_bytes(n, k, k));
     if (!rc) {
         // Galerkin H = V^T (A V); MinRes H = (A V)^T (A V)
@@ -226,17 +280,17 @@ int defl_finish(tgdk_op op, int transpose, double* V64, int k, int store, tgdk_d
             hipStreamSynchronize(s) != hipSuccess)
             rc = fail(TGDK_E_HIP, "forming H failed");
     }
-    if (dG) (void)hipFree(dG);
+    if (dG) ctx->pool.put(dG);
     void* W = nullptr;  // the stored left basis (MinRes only)
     if (minres && !rc) {
         W = store == TGDK_F32 ? (void*)W32 : (void*)AV;
-        if (store == TGDK_F32) (void)hipFree(AV);
+        if (store == TGDK_F32) ctx->pool.put(AV);
     } else {
-        (void)hipFree(AV);
-        if (W32) (void)hipFree(W32);
+        ctx->pool.put(AV);
+        if (W32) ctx->pool.put(W32);
     }
     if (rc) {
-        if (V32) (void)hipFree(V32);
+        if (V32) ctx->pool.put(V32);
         return rc;
     }
     tgdk_defl d = new tgdk_defl_s();
@@ -252,14 +306,14 @@ int defl_finish(tgdk_op op, int transpose, double* V64, int k, int store, tgdk_d
     d->mvp_build = k;
     if ((rc = defl_factor(d, minres ? "projection matrix H = (AV)^T AV is singular"
                                     : "projection matrix H = V^T A V is singular"))) {
-        if (V32) (void)hipFree(V32);
-        if (W) (void)hipFree(W);
+        if (V32) ctx->pool.put(V32);
+        if (W) ctx->pool.put(W);
         delete d;
         return rc;
     }
     if (store == TGDK_F32) {
         d->V = V32;
-        (void)hipFree(V64);
+        ctx->pool.put(V64);
     } else {
         d->V = V64;
     }
@@ -541,16 +595,16 @@ int tgdk_defl_prolongate(tgdk_defl cs, tgdk_op fine, int store_dtype, tgdk_defl*
     TGDK_HIP(hipSetDevice(fine->ctx->device));
     const int k = cs->k;
     double* PW = nullptr;
-    if ((rc = dev_alloc(&PW, (size_t)fine->N * k))) return rc;
+    if ((rc = pool_alloc(fine->ctx, &PW, (size_t)fine->N * k))) return rc;
     tgdk_op c = cs->op;
     launch_prolong(fine->dim, c->n[0], c->n[1], fine->dim == 3 ? c->n[2] : 1, (const double*)cs->V, PW, k,
                    fine->ctx->stream);
     if ((rc = cholqr2(fine->ctx, PW, fine->N, k))) {
-        (void)hipFree(PW);
+        fine->ctx->pool.put(PW);
         return rc;
     }
     rc = defl_finish(fine, cs->transpose, PW, k, store_dtype, out, TGDK_PROJ_GALERKIN);
-    if (rc) (void)hipFree(PW);
+    if (rc) fine->ctx->pool.put(PW);
     return rc;
 }
 
@@ -559,15 +613,15 @@ int tgdk_defl_from_basis(tgdk_op op, const double* W, int k, int transpose, int 
     if (store_dtype != TGDK_F64 && store_dtype != TGDK_F32) return fail(TGDK_E_INVALID, "store dtype");
     TGDK_HIP(hipSetDevice(op->ctx->device));
     double* V = nullptr;
-    int rc = dev_alloc(&V, (size_t)op->N * k);
+    int rc = pool_alloc(op->ctx, &V, (size_t)op->N * k);
     if (rc) return rc;
     TGDK_HIP(hipMemcpyAsync(V, W, (size_t)op->N * k * sizeof(double), hipMemcpyDeviceToDevice, op->ctx->stream));
     if ((rc = cholqr2(op->ctx, V, op->N, k))) {
-        (void)hipFree(V);
+        op->ctx->pool.put(V);
         return rc;
     }
     rc = defl_finish(op, transpose ? 1 : 0, V, k, store_dtype, out, TGDK_PROJ_GALERKIN);
-    if (rc) (void)hipFree(V);
+    if (rc) op->ctx->pool.put(V);
     return rc;
 }
 
@@ -576,7 +630,7 @@ int tgdk_defl_minres(tgdk_defl g, tgdk_defl* out) {
     if (g->precond) return fail(TGDK_E_INVALID, "a preconditioned space has no MinRes variant");
     TGDK_HIP(hipSetDevice(g->ctx->device));
     double* V = nullptr;
-    int rc = dev_alloc(&V, (size_t)g->n * g->k);
+    int rc = pool_alloc(g->ctx, &V, (size_t)g->n * g->k);
     if (rc) return rc;
     if (g->store == TGDK_F64)
         TGDK_HIP(hipMemcpyAsync(V, g->V, (size_t)g->n * g->k * sizeof(double), hipMemcpyDeviceToDevice,
@@ -584,7 +638,7 @@ int tgdk_defl_minres(tgdk_defl g, tgdk_defl* out) {
     else
         launch_to_f64((const float*)g->V, V, (long long)g->n * g->k, g->ctx->stream);
     rc = defl_finish(g->op, g->transpose, V, g->k, g->store, out, TGDK_PROJ_MINRES);
-    if (rc) (void)hipFree(V);
+    if (rc) g->ctx->pool.put(V);
     return rc;
 }
 
@@ -602,13 +656,13 @@ int tgdk_defl_precond(tgdk_defl g, tgdk_precond_fn fn, void* user, tgdk_defl* ou
     double *V = nullptr, *Z = nullptr, *AZ = nullptr, *dG = nullptr;
     int rc;
     auto release = [&]() {
-        if (V) (void)hipFree(V);
-        if (Z) (void)hipFree(Z);
-        if (AZ) (void)hipFree(AZ);
-        if (dG) (void)hipFree(dG);
+        if (V) ctx->pool.put(V);
+        if (Z) ctx->pool.put(Z);
+        if (AZ) ctx->pool.put(AZ);
+        if (dG) ctx->pool.put(dG);
     };
-    if ((rc = dev_alloc(&V, (size_t)n * k)) || (rc = dev_alloc(&Z, (size_t)n * k)) ||
-        (rc = dev_alloc(&AZ, (size_t)n * k)) || (rc = dev_alloc(&dG, (size_t)k * k))) {
+    if ((rc = pool_alloc(ctx, &V, (size_t)n * k)) || (rc = pool_alloc(ctx, &Z, (size_t)n * k)) ||
+        (rc = pool_alloc(ctx, &AZ, (size_t)n * k)) || (rc = pool_alloc(ctx, &dG, (size_t)k * k))) {
         release();
         return rc;
     }
@@ -626,8 +680,8 @@ int tgdk_defl_precond(tgdk_defl g, tgdk_precond_fn fn, void* user, tgdk_defl* ou
         release();
         return fail(TGDK_E_HIP, "forming H failed");
     }
-    (void)hipFree(AZ);
-    (void)hipFree(dG);
+    ctx->pool.put(AZ);
+    ctx->pool.put(dG);
     AZ = dG = nullptr;
     tgdk_defl d = new tgdk_defl_s();
     d->ctx = ctx;
@@ -677,11 +731,11 @@ int tgdk_defl_copy(tgdk_defl d, double* V_out, double* H_out) {
 int tgdk_defl_destroy(tgdk_defl d) {
     if (!d) return TGDK_OK;
     (void)hipSetDevice(d->ctx->device);
-    if (d->V) (void)hipFree(d->V);
-    if (d->W) (void)hipFree(d->W);
-    if (d->d_lu) (void)hipFree(d->d_lu);
-    if (d->d_piv) (void)hipFree(d->d_piv);
-    if (d->d_hinv) (void)hipFree(d->d_hinv);
+    d->ctx->pool.put(d->V);
+    d->ctx->pool.put(d->W);
+    d->ctx->pool.put(d->d_lu);
+    d->ctx->pool.put(d->d_piv);
+    d->ctx->pool.put(d->d_hinv);
     delete d;
     return TGDK_OK;
 }

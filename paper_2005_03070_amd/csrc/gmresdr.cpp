@@ -95,17 +95,15 @@ extern "C" int tgdk_coarse_setup(tgdk_op op, const double* b, double* x, const t
     double *V = nullptr, *Vt = nullptr, *w = nullptr, *Hd = nullptr, *dP = nullptr;
     const size_t hsz = (size_t)(m + 1) * m;
     auto cleanup = [&]() {
-        if (V) (void)hipFree(V);
-        if (Vt) (void)hipFree(Vt);
-        if (w) (void)hipFree(w);
-        if (Hd) (void)hipFree(Hd);
-        if (dP) (void)hipFree(dP);
+        ctx->pool.put(V);
+        ctx->pool.put(Vt);
+        ctx->pool.put(w);
+        ctx->pool.put(Hd);
+        ctx->pool.put(dP);
     };
-    if (hipMalloc((void**)&V, sizeof(double) * n * (m + 1)) != hipSuccess ||
-        hipMalloc((void**)&Vt, sizeof(double) * n * (m + 1)) != hipSuccess ||
-        hipMalloc((void**)&w, sizeof(double) * n * (prm->precond ? 2 : 1)) != hipSuccess ||
-        hipMalloc((void**)&Hd, sizeof(double) * (2 * hsz + m + 16)) != hipSuccess ||
-        hipMalloc((void**)&dP, sizeof(double) * (m + 1) * (m + 2)) != hipSuccess) {
+    if (pool_alloc(ctx, &V, (size_t)n * (m + 1)) || pool_alloc(ctx, &Vt, (size_t)n * (m + 1)) ||
+        pool_alloc(ctx, &w, (size_t)n * (prm->precond ? 2 : 1)) || pool_alloc(ctx, &Hd, 2 * hsz + m + 16) ||
+        pool_alloc(ctx, &dP, (size_t)(m + 1) * (m + 2))) {
         cleanup();
         return fail(TGDK_E_NOMEM, "GMRES-DR workspace allocation failed");
     }
@@ -217,14 +215,14 @@ extern "C" int tgdk_coarse_setup(tgdk_op op, const double* b, double* x, const t
             if (cyc % 5 == 1 || done) {  // loss of orthogonality of the basis
                 std::vector<double> G((size_t)(m + 1) * (m + 1));
                 double* dG = nullptr;
-                if (hipMalloc((void**)&dG, sizeof(double) * G.size()) == hipSuccess &&
+                if (pool_alloc(ctx, &dG, G.size()) == TGDK_OK &&
                     ctx->partial.ensure(gram_partial_bytes(n, m + 1, m + 1)) == TGDK_OK) {
                     launch_gram(V, 0, n, m + 1, V, 0, n, m + 1, n, dG, (double*)ctx->partial.p, ctx->counters, s);
                     (void)hipMemcpy(G.data(), dG, sizeof(double) * G.size(), hipMemcpyDeviceToHost);
                     for (int i = 0; i <= m; ++i)
                         for (int j = 0; j <= m; ++j)
                             orth = std::max(orth, std::fabs(G[(size_t)i * (m + 1) + j] - (i == j ? 1.0 : 0.0)));
-                    (void)hipFree(dG);
+                    ctx->pool.put(dG);
                     (void)ctx->partial.ensure((size_t)gs_blocks(n) * (MAXK + 1) * sizeof(double));
                     part = (double*)ctx->partial.p;
                 }
@@ -270,7 +268,7 @@ extern "C" int tgdk_coarse_setup(tgdk_op op, const double* b, double* x, const t
         TGDK_HIP(hipMemcpyAsync(dP, Qc.data(), sizeof(double) * Qc.size(), hipMemcpyHostToDevice, s));
         launch_vmul(V, n, m + 1, dP, kk + 1, Vt, n, n, s);
         if (done || cyc == maxcyc) {
-            if (hipMalloc((void**)&W, sizeof(double) * n * kk) != hipSuccess) {
+            if (pool_alloc(ctx, &W, (size_t)n * kk)) {
                 cleanup();
                 return fail(TGDK_E_NOMEM, "basis allocation failed");
             }
@@ -320,7 +318,7 @@ extern "C" int tgdk_coarse_setup(tgdk_op op, const double* b, double* x, const t
     }
     if (rc) {
         cleanup();
-        if (W) (void)hipFree(W);
+        ctx->pool.put(W);
         return rc;
     }
     // final true residual of the coarse solution: ||A x - b||
@@ -335,7 +333,7 @@ extern "C" int tgdk_coarse_setup(tgdk_op op, const double* b, double* x, const t
     tgdk_defl d = nullptr;
     rc = defl_finish(op, tr, W, kk, TGDK_F64, &d, TGDK_PROJ_GALERKIN);
     if (rc) {
-        (void)hipFree(W);
+        ctx->pool.put(W);
         return rc;
     }
     *out = d;

@@ -707,14 +707,15 @@ static int gmres_single(tgdk_ctx ctx, const ProbSpec& p, const tgdk_solve_params
     double *V = nullptr, *w = nullptr, *Hd = nullptr, *dy = nullptr, *pz = nullptr;
     const size_t hsz = (size_t)(m + 1) * m;
     const bool pre = prm->precond != nullptr;
-    if (hipMalloc((void**)&V, sizeof(double) * n * (m + 1)) != hipSuccess)
-        return fail(TGDK_E_NOMEM, "GMRES basis allocation failed");
-    if (hipMalloc((void**)&w, sizeof(double) * n * (pre ? 3 : 1)) != hipSuccess ||
-        hipMalloc((void**)&Hd, sizeof(double) * (2 * hsz + m + 8)) != hipSuccess ||
-        hipMalloc((void**)&dy, sizeof(double) * (m + 1)) != hipSuccess) {
-        (void)hipFree(V);
-        if (w) (void)hipFree(w);
-        if (Hd) (void)hipFree(Hd);
+    auto release = [&]() {
+        ctx->pool.put(V);
+        ctx->pool.put(w);
+        ctx->pool.put(Hd);
+        ctx->pool.put(dy);
+    };
+    if (pool_alloc(ctx, &V, (size_t)n * (m + 1)) || pool_alloc(ctx, &w, (size_t)n * (pre ? 3 : 1)) ||
+        pool_alloc(ctx, &Hd, 2 * hsz + m + 8) || pool_alloc(ctx, &dy, (size_t)m + 1)) {
+        release();
         return fail(TGDK_E_NOMEM, "GMRES workspace allocation failed");
     }
     double* H1 = Hd;
@@ -797,10 +798,7 @@ static int gmres_single(tgdk_ctx ctx, const ProbSpec& p, const tgdk_solve_params
         TGDK_HIP(hipGetLastError());
         TGDK_HIP(hipStreamSynchronize(s));
     }
-    (void)hipFree(V);
-    (void)hipFree(w);
-    (void)hipFree(Hd);
-    (void)hipFree(dy);
+    release();
     if (rc) return rc;
     const double secs = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
     return finish_group(g, ps, rep, secs, &extra, &cyc_steps);
@@ -831,12 +829,12 @@ static int idr_single(tgdk_ctx ctx, const ProbSpec& p, int s, const double* shad
     const size_t off_pz = off_st + align256(sizeof(IdrState));  // preconditioner output
     const size_t bytes = off_pz + (prm->precond ? align256((size_t)n * 8) : 0);
     char* wk = nullptr;
-    if (hipMalloc((void**)&wk, bytes) != hipSuccess) return fail(TGDK_E_NOMEM, "IDR workspace allocation failed");
+    if (pool_alloc(ctx, &wk, bytes)) return fail(TGDK_E_NOMEM, "IDR workspace allocation failed");
     double* P64 = (double*)(wk + off_p64);
     IdrState* d_st = (IdrState*)(wk + off_st);
     auto done = [&](int code) {
         (void)hipStreamSynchronize(hs);
-        (void)hipFree(wk);
+        ctx->pool.put(wk);
         return code;
     };
 #define IDR_HIP(call)                                                                        \
