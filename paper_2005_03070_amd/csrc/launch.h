@@ -53,6 +53,13 @@ int step_blocks_per_cu(int inner_f32, int var, int tile_id);
 // probs), then launches teams * args.team workgroups cooperatively.
 hipError_t launch_resident2d(int inner_f32, int var, const ResArgs& args, const DevProb* probs, int teams,
                              hipStream_t s);
+void launch_res_setup(const ResArgs& args, const DevProb* probs, int teams, hipStream_t s);
+// The same for one IDR(s) solve (P64: the s orthonormal shadow columns);
+// resident_idr_rows: grid rows of a tile for s (0: s too large).
+constexpr int RES_IDR_SMAX = 8;
+int resident_idr_rows(int s);
+hipError_t launch_resident_idr(int inner_f32, int var, const ResArgs& args, const DevProb* prob, const double* P64,
+                               int s, double kappa, hipStream_t stream);
 
 // IDR(s) inner cycles (kernels_idr.hip): what = one of the IDR_* actions,
 // k = the step of the round for IDR_DIR, IDR_ALPHA, IDR_ORTH, IDR_UPD.

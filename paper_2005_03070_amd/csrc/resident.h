@@ -138,18 +138,17 @@ __device__ __forceinline__ double row_sum(double v) {
     return v;
 }
 // Several values at once: lane i of a row gets value i's sum over the row (i <
-// NV <= 5).  Two values share a register from the first step on (each lane
+// NV <= 9).  Two values share a register from the first step on (each lane
 // keeps one and hands the other to its neighbour), four from the second, so
 // five sums take 39 vector instructions instead of 60.
 template <int NV>
-__device__ __forceinline__ double row_sums(const double (&a)[NV]) {
-    static_assert(NV >= 1 && NV <= 5, "values");
+__device__ __forceinline__ double row_sums(const double* a) {
     const int lane = threadIdx.x & 63;
+    const bool odd = lane & 1, hi = lane & 2;
+    auto pair = [&](double x, double y) { return (odd ? y : x) + dpp_move<0xB1, 0xf>(odd ? x : y); };
     if constexpr (NV == 1) {
         return row_sum(a[0]);
-    } else {
-        const bool odd = lane & 1, hi = lane & 2;
-        auto pair = [&](double x, double y) { return (odd ? y : x) + dpp_move<0xB1, 0xf>(odd ? x : y); };
+    } else if constexpr (NV <= 4) {
         double r;
         const double ab = pair(a[0], a[1]);
         if constexpr (NV == 2) {
@@ -160,11 +159,17 @@ __device__ __forceinline__ double row_sums(const double (&a)[NV]) {
         }
         r += dpp_move<0x124, 0xf>(r);
         r += dpp_move<0x128, 0xf>(r);
-        if constexpr (NV == 5) {
-            const double e = row_sum(a[4]);
-            r = (lane & 15) == 4 ? e : r;
-        }
         return r;
+    } else {
+        static_assert(NV <= 9, "values");
+        const double r = row_sums<4>(a);
+        if constexpr (NV <= 8) {
+            const double x = row_sums<NV - 4>(a + 4);  // lane i of four: value 4 + i
+            return (lane & 15) < 4 ? r : x;
+        } else {
+            const double x = row_sums<4>(a + 4), y = row_sum(a[8]);
+            return (lane & 15) < 4 ? r : (lane & 15) < 8 ? x : y;
+        }
     }
 }
 // The same value, unknown to the compiler: what is computed from it stays

@@ -196,11 +196,20 @@ struct ExtWs {
 // Up to that size it is faster everywhere: 63^2 (one tile) 14.9 -> 3.1 us per
 // iteration, 1023^2 (256 tiles) 31.8 -> 7.5 us; beyond it the tiles do not fit.
 // With the measurement of single step launches on, the step kernel runs.
-static int resident_team(tgdk_ctx ctx, const std::vector<ProbSpec>& ps, const tgdk_solve_params* prm) {
-    if (ps[0].op->dim != 2 || prm->method != TGDK_BICGSTAB_PROJ || ctx->time_which) return 0;
+// IDR(s) has the same scheme for s <= 8 without a preconditioner (idr_s; 64 x
+// 32 tiles past s = 4): 511^2 with s = 4 30 -> 10 us per operator application.
+static int resident_team(tgdk_ctx ctx, const std::vector<ProbSpec>& ps, const tgdk_solve_params* prm, int idr_s) {
+    if (ps[0].op->dim != 2) return 0;
+    int rows = RES_TILE;
+    if (prm->method == TGDK_IDRS_PROJ) {
+        rows = prm->precond ? 0 : resident_idr_rows(idr_s);
+        if (rows == 0) return 0;
+    } else if (prm->method != TGDK_BICGSTAB_PROJ || ctx->time_which) {
+        return 0;
+    }
     long long team = 0;
     for (const auto& p : ps) {
-        const long long tx = (p.op->n[0] + RES_TILE - 1) / RES_TILE, ty = (p.op->n[1] + RES_TILE - 1) / RES_TILE;
+        const long long tx = (p.op->n[0] + RES_TILE - 1) / RES_TILE, ty = (p.op->n[1] + rows - 1) / rows;
         team = std::max(team, tx * ty);
     }
     return team <= std::min(ctx->num_cus, 256) ? (int)team : 0;
@@ -220,7 +229,7 @@ static void set_space(DevProb& P, tgdk_defl d) {
 // Fills the device-side group description and workspaces (allocated in the
 // context's grow-only buffer, or laid out in ext).
 static int build_group(tgdk_ctx ctx, const std::vector<ProbSpec>& ps, const tgdk_solve_params* prm, Group& g,
-                       const ExtWs* ext = nullptr) {
+                       const ExtWs* ext = nullptr, int idr_s = 0) {
     g.ctx = ctx;
     g.nprob = (int)ps.size();
     g.dim = ps[0].op->dim;
@@ -261,7 +270,7 @@ static int build_group(tgdk_ctx ctx, const std::vector<ProbSpec>& ps, const tgdk
     // phases at n_x = 255); x, b and V keep the caller's pitch n_x.  The
     // other drivers' kernels and the 2-D tile paths assume pitch n_x.
     const bool padded = g.dim == 3 && prm->method == TGDK_BICGSTAB_PROJ;
-    g.team = resident_team(ctx, ps, prm);
+    g.team = resident_team(ctx, ps, prm, idr_s);
     std::vector<size_t> nstore(g.nprob);  // elements per stored vector
     for (int j = 0; j < g.nprob; ++j) {
         const tgdk_op op = ps[j].op;
@@ -369,7 +378,7 @@ static int build_group(tgdk_ctx ctx, const std::vector<ProbSpec>& ps, const tgdk
         in.rtol = prm->rtol;
         in.fp32_floor = prm->fp32_floor > 0 ? prm->fp32_floor : 1e-4;
         in.nu0_in = prm->nu0;
-        in.method = METHOD_BICGSTAB;
+        in.method = prm->method == TGDK_IDRS_PROJ ? METHOD_IDR : METHOD_BICGSTAB;
         in.ncyc = prm->ncyc;
         in.max_extra = prm->max_extra_cycles >= 0 ? prm->max_extra_cycles : prm->ncyc;
         in.maxit = prm->maxit_cycle > 0 ? prm->maxit_cycle : 100000;
@@ -608,19 +617,23 @@ static int predict_steps(const Mirror& m, Predict& pr) {
 }
 
 // The chip-resident solve: one launch runs every system of the group to its
-// end; the host waits for it.
+// end; the host waits for it.  idr_s > 0: IDR(s) with the shadow columns P64.
 static int resident_group(Group& g, const std::vector<ProbSpec>& ps, tgdk_solve_report* reps,
-                          std::chrono::steady_clock::time_point t0) {
+                          std::chrono::steady_clock::time_point t0, int idr_s = 0, const double* P64 = nullptr,
+                          double kappa = 0.0) {
     tgdk_ctx ctx = g.ctx;
     hipStream_t s = ctx->stream;
-    TGDK_HIP(launch_resident2d(g.inner_f32, g.var, g.res, g.probs.data(), g.teams, s));
+    if (idr_s > 0)
+        TGDK_HIP(launch_resident_idr(g.inner_f32, g.var, g.res, g.probs.data(), P64, idr_s, kappa, s));
+    else
+        TGDK_HIP(launch_resident2d(g.inner_f32, g.var, g.res, g.probs.data(), g.teams, s));
     TGDK_HIP(hipEventRecord(ctx->events[0], s));
     int rc = wait_event(ctx->events[0]);
     if (rc) return rc;
     const double secs = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
     unsigned ctl[2] = {0, 0};
     TGDK_HIP(hipMemcpyAsync(ctl, g.res.ctl, sizeof(ctl), hipMemcpyDeviceToHost, s));
-    rc = finish_group(g, ps, reps, secs, nullptr);
+    rc = finish_group(g, ps, reps, secs, nullptr, nullptr, idr_s);
     return ctl[1] ? fail(TGDK_E_HIP, "the resident solve stopped making progress") : rc;
 }
 
@@ -814,7 +827,7 @@ static int idr_single(tgdk_ctx ctx, const ProbSpec& p, int s, const double* shad
     const auto t0 = std::chrono::steady_clock::now();
     std::vector<ProbSpec> ps{p};
     Group g;
-    int rc = build_group(ctx, ps, prm, g);
+    int rc = build_group(ctx, ps, prm, g, nullptr, s);
     if (rc) return rc;
     if ((rc = ensure_events(ctx, 2))) return rc;
     hipStream_t hs = ctx->stream;
@@ -844,6 +857,7 @@ static int idr_single(tgdk_ctx ctx, const ProbSpec& p, int s, const double* shad
     } while (0)
     IDR_HIP(hipMemcpyAsync(P64, shadow, sn * 8, hipMemcpyDeviceToDevice, hs));
     if ((rc = cholqr2(ctx, P64, n, s))) return done(rc == TGDK_E_SINGULAR ? fail(rc, "shadow space is rank deficient") : rc);
+    if (g.team) return done(resident_group(g, ps, rep, t0, s, P64, kappa));
     if (f32) launch_to_f32(P64, (float*)(wk + off_p), (long long)sn, hs);
     IdrState h;
     memset(&h, 0, sizeof(h));

@@ -157,7 +157,8 @@ struct DevProb {
 // Chip-resident 2-D solve (kernels_resident2d.hip): teams of `team`
 // workgroups, one per RES_TILE x RES_TILE tile, take systems from a queue.
 constexpr int RES_TILE = 64;
-constexpr int RES_NSUM = 5;   // most sums of one exchange
+constexpr int RES_NSUM = 9;   // most sums of one exchange
+constexpr int RES_TOTALS = 16;  // words of a copy of their totals
 constexpr int RES_COPIES = 16;  // copies of an exchange's totals (read by different workgroups)
 constexpr int RES_ARGPROBS = 4;  // descriptors passed in the set-up kernel's arguments
 // A solve's parameters, the same for every system (names as in SolveState).
@@ -183,7 +184,7 @@ struct ResProbs {
 // each), the column partials and values of c = V^T r.
 inline long long res_exchange_words(int team, int kmax) {
     const long long tp = (team + 63) / 64 * 64;
-    return 3 * RES_NSUM * tp + 3 * RES_COPIES * 8 + 3LL * team * 4 * RES_TILE + kmax * (tp + 1) + 15;
+    return 3 * RES_NSUM * tp + 3 * RES_COPIES * RES_TOTALS + 3LL * team * 4 * RES_TILE + kmax * (tp + 1) + 15;
 }
 
 constexpr int NSLOTLOG = 1 << 15;

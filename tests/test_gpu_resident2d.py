@@ -1,5 +1,5 @@
-"""The chip-resident 2-D BiCGStab solve (kernels_resident2d.hip) at the edges
-of its tiles, teams and queue, against the oracle's operators.
+"""The chip-resident 2-D solves (kernels_resident2d.hip, kernels_resident_idr.hip)
+at the edges of their tiles, teams and queue, against the oracle's operators.
 
 A solve stops at a true relative residual of 1e-10, so the bounds are the
 method's own: ||b - A x|| <= 1e-10 ||b|| up to the rounding of forming the
@@ -123,3 +123,30 @@ def test_largest_space_and_step_kernel_agree():
     assert torch.linalg.norm(x - xs) <= 1e-11 * torch.linalg.norm(xs)
     assert (r[0].cycles, r[0].mvp_inner, r[0].mvp_boundary) == (rs[0].cycles, rs[0].mvp_inner, rs[0].mvp_boundary)
     np.testing.assert_allclose(np.array(r[0].first_scalars), np.array(rs[0].first_scalars), rtol=1e-9)
+
+
+@pytest.mark.parametrize("dims", [(20, 11), (64, 32), (65, 33), (130, 190), (300, 260)])
+@pytest.mark.parametrize("s", [1, 2, 3, 4, 5, 8])
+def test_idr_tile_edges(dims, s):
+    """IDR(s): 64 x 64 tiles to s = 4, 64 x 32 beyond; precision, transpose and
+    coefficient arrays alternate over the cases."""
+    n = dims[0] * dims[1]
+    transpose, precision = bool(s % 2), ("fp32_ir" if s in (2, 5) else "fp64")
+    beta = (6.0, 3.0)
+    if s in (3, 8):
+        kc = W.kfield(dims, 3)
+        oop, op = O.div_k(dims, kc, beta), tg().Operator.div_k(dims, torch.tensor(kc, device=DEV), beta)
+    else:
+        oop, op = O.const_cd(dims, beta), tg().Operator.const_cd(dims, beta, device=DEV)
+    b = W.rhs(n, 19)
+    defl = None if s == 4 else tg().defl_from_basis(op, torch.tensor(_basis(dims, 5, 5), device=DEV),
+                                                    transpose=transpose)
+    shadow = torch.tensor(W.shadow_draw(n, s, 7), device=DEV)
+    x, rep = tg().solve_idr(op, torch.tensor(b, device=DEV), s=s, shadow=shadow, defl=defl, precision=precision,
+                            rtol=1e-9, max_extra=100, transpose=transpose)
+    r = b - (O.apply_transpose if transpose else O.apply)(oop, x.cpu().numpy())
+    assert rep.status == 0 and np.linalg.norm(r) <= 1.01e-9 * np.linalg.norm(b)
+    assert rep.mvp_inner == sum(rep.cycle_mvps)
+    if s not in (3, 8):
+        xs = ODS.solve(oop, b, transpose=transpose)
+        assert np.linalg.norm(x.cpu().numpy() - xs) <= 1.02e-9 * np.linalg.norm(b) / _lambda(dims)
