@@ -43,6 +43,47 @@ void DevBuf::release() {
     cap = 0;
 }
 
+int ArnoldiSteps::init(const DevOp& op, int m, double* H1, double* H2, double* nrm) {
+    a_.op = op;
+    a_.H1 = H1;
+    a_.H2 = H2;
+    a_.nrm = nrm;
+    a_.ldh = m + 1;
+    a_.pmax = m;
+    rq = arnoldi2d_rows(op, m, std::min(ctx_->num_cus, 256), &a_.team);
+    if (!rq) return TGDK_OK;
+    char* p = nullptr;
+    const int rc = pool_alloc(ctx_, &p, (size_t)256 + (size_t)arnoldi2d_words(a_.team, a_.pmax) * 8);
+    if (rc) {
+        rq = 0;
+        return rc;
+    }
+    block_ = p;
+    a_.ctl = (unsigned*)p;
+    a_.xch = p + 256;
+    return TGDK_OK;
+}
+
+int ArnoldiSteps::run(int j0, int j1, bool reorth, double* V) {
+    a_.V = V;
+    a_.j0 = j0;
+    a_.j1 = j1;
+    a_.reorth = reorth;
+    TGDK_HIP(launch_arnoldi2d(a_, rq, ctx_->stream));
+    return TGDK_OK;
+}
+
+int ArnoldiSteps::wait() {
+    if (rq) TGDK_HIP(hipMemcpyAsync(ctl_, a_.ctl, sizeof(ctl_), hipMemcpyDeviceToHost, ctx_->stream));
+    TGDK_HIP(hipStreamSynchronize(ctx_->stream));
+    return rq && ctl_[1] ? fail(TGDK_E_HIP, "the Arnoldi steps stopped making progress") : TGDK_OK;
+}
+
+void ArnoldiSteps::release() {
+    if (block_) ctx_->pool.put(block_);
+    block_ = nullptr;
+}
+
 void DevPool::trim(size_t room) {
     for (size_t i = 0; i < idle.size();) {  // oldest first
         if (now - idle[i].stamp <= POOL_AGE && held + room <= POOL_BYTES) {

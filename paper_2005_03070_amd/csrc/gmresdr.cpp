@@ -94,7 +94,9 @@ extern "C" int tgdk_coarse_setup(tgdk_op op, const double* b, double* x, const t
 
     double *V = nullptr, *Vt = nullptr, *w = nullptr, *Hd = nullptr, *dP = nullptr;
     const size_t hsz = (size_t)(m + 1) * m;
+    ArnoldiSteps steps1(ctx);  // a cycle's steps in one launch, where that applies
     auto cleanup = [&]() {
+        steps1.release();
         ctx->pool.put(V);
         ctx->pool.put(Vt);
         ctx->pool.put(w);
@@ -123,7 +125,21 @@ extern "C" int tgdk_coarse_setup(tgdk_op op, const double* b, double* x, const t
     // A M^{-1}; x accumulates u and becomes M^{-1} u at the end
     double* pz = prm->precond ? w + n : nullptr;
     int prc = TGDK_OK;
-    auto arnoldi = [&](int j0) {
+    if (!pz && (rc = steps1.init(dop, m, H1, H2, Nd))) {
+        cleanup();
+        return rc;
+    }
+    // steps j0 .. m - 1; after a restart column j0 is first re-orthogonalised
+    // against the ones before it
+    auto arnoldi = [&](int j0) -> int {
+        if (steps1.rq) return steps1.run(j0, m, j0 > 0, V);
+        if (j0 > 0) {
+            double* vk = V + (size_t)j0 * n;
+            launch_gs_dot(V, n, j0, vk, n, H1, part, cnt, s);  // column 0 of H1/H2 is scratch here
+            launch_gs_update_dot(V, n, j0, vk, H1, n, H2, part, cnt, s);
+            launch_gs_update_norm(V, n, j0, vk, H2, n, dsc + 2, part, cnt, s);
+            launch_scale(vk, vk, dsc + 2, n, s);
+        }
         for (int j = j0; j < m; ++j) {
             if (pz) {
                 if (!prc) prc = prm->precond(prm->precond_user, V + (size_t)j * n, pz, 1);
@@ -136,13 +152,15 @@ extern "C" int tgdk_coarse_setup(tgdk_op op, const double* b, double* x, const t
             launch_gs_update_norm(V, n, j + 1, w, H2 + (size_t)j * (m + 1), n, Nd + j, part, cnt, s);
             launch_scale(w, V + (size_t)(j + 1) * n, Nd + j, n, s);
         }
+        return TGDK_OK;
     };
     std::vector<double> h1(hsz), h2(hsz), nrm(m);
     auto fetch_columns = [&](std::vector<double>& Hbar, int j0) -> int {
         TGDK_HIP(hipMemcpyAsync(h1.data(), H1, sizeof(double) * hsz, hipMemcpyDeviceToHost, s));
         TGDK_HIP(hipMemcpyAsync(h2.data(), H2, sizeof(double) * hsz, hipMemcpyDeviceToHost, s));
         TGDK_HIP(hipMemcpyAsync(nrm.data(), Nd, sizeof(double) * m, hipMemcpyDeviceToHost, s));
-        TGDK_HIP(hipStreamSynchronize(s));
+        const int wrc = steps1.wait();
+        if (wrc) return wrc;
         for (int j = j0; j < m; ++j) {
             for (int i = 0; i <= j; ++i)
                 Hbar[(size_t)i * m + j] = h1[(size_t)j * (m + 1) + i] + h2[(size_t)j * (m + 1) + i];
@@ -163,7 +181,10 @@ extern "C" int tgdk_coarse_setup(tgdk_op op, const double* b, double* x, const t
     }
     const double bnorm = beta;
     launch_scale(b, V, dsc, n, s);
-    arnoldi(0);
+    if ((rc = arnoldi(0))) {
+        cleanup();
+        return rc;
+    }
     std::vector<double> Hbar(hsz, 0.0), c(m + 1, 0.0), y(m), q(m + 1);
     if ((rc = fetch_columns(Hbar, 0))) {
         cleanup();
@@ -296,12 +317,10 @@ extern "C" int tgdk_coarse_setup(tgdk_op op, const double* b, double* x, const t
         }
         std::swap(V, Vt);
         // re-orthogonalise v_{k+1} against v_1..v_k, then continue Arnoldi
-        double* vk = V + (size_t)kk * n;
-        launch_gs_dot(V, n, kk, vk, n, H1, part, cnt, s);  // column 0 of H1/H2 is scratch here
-        launch_gs_update_dot(V, n, kk, vk, H1, n, H2, part, cnt, s);
-        launch_gs_update_norm(V, n, kk, vk, H2, n, dsc + 2, part, cnt, s);
-        launch_scale(vk, vk, dsc + 2, n, s);
-        arnoldi(kk);
+        if ((rc = arnoldi(kk))) {
+            cleanup();
+            return rc;
+        }
         mvps += m - kk;
         Hbar = Hn;
         c = cn;

@@ -133,6 +133,23 @@ struct tgdk_defl_s {
 
 namespace tgdk {
 
+// A cycle's Arnoldi steps in one launch (kernels_arnoldi2d.hip) for a basis of
+// up to m + 1 columns; H1, H2 with columns of m + 1, nrm: m values.
+struct ArnoldiSteps {
+    explicit ArnoldiSteps(tgdk_ctx ctx) : ctx_(ctx) {}
+    int rq = 0;  // 0 (not initialised, or the one-launch form does not apply): the steps are launched one by one
+    int init(const DevOp& op, int m, double* H1, double* H2, double* nrm);
+    int run(int j0, int j1, bool reorth, double* V);  // enqueue, on basis V
+    int wait();  // for the stream, in either form; an error if the kernel gave up
+    void release();
+
+private:
+    tgdk_ctx ctx_;
+    ArnArgs a_;
+    void* block_ = nullptr;
+    unsigned ctl_[2] = {0, 0};
+};
+
 DevOp make_devop(const tgdk_op_s* op, int transpose);
 // Memory from a context's pool; TGDK_E_NOMEM (with *p null) when there is none.
 template <class T>

@@ -61,6 +61,26 @@ int resident_idr_rows(int s);
 hipError_t launch_resident_idr(int inner_f32, int var, const ResArgs& args, const DevProb* prob, const double* P64,
                                int s, double kappa, hipStream_t stream);
 
+// Arnoldi steps j0 .. j1 - 1 on a 2-D grid in one launch: column j of V
+// multiplied by A, orthogonalised twice against columns 0 .. j (coefficients
+// to H1 and H2, column j at j ldh), its norm to nrm[j], normalised into column
+// j + 1.  reorth: column j0 itself is first orthogonalised against the ones
+// before it and normalised.  xch: arnoldi2d_words(team, pmax) words, ctl: two
+// words ([1] raised when a wait has timed out).
+struct ArnArgs {
+    DevOp op;
+    double* V;
+    double *H1, *H2, *nrm;
+    int ldh, j0, j1, reorth, team, pmax;
+    void* xch;
+    unsigned* ctl;
+};
+// Rows per wave of a tile (0: the one-launch steps do not apply: 3-D, more than
+// 128 columns, or more tiles than max_team), and the workgroups they need.
+int arnoldi2d_rows(const DevOp& op, int pmax, int max_team, int* team);
+long long arnoldi2d_words(int team, int pmax);
+hipError_t launch_arnoldi2d(const ArnArgs& args, int rq, hipStream_t s);
+
 // IDR(s) inner cycles (kernels_idr.hip): what = one of the IDR_* actions,
 // k = the step of the round for IDR_DIR, IDR_ALPHA, IDR_ORTH, IDR_UPD.
 enum : int {

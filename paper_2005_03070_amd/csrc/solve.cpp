@@ -740,6 +740,8 @@ static int gmres_single(tgdk_ctx ctx, const ProbSpec& p, const tgdk_solve_params
     std::vector<long long> extra(1, 0);
     std::vector<int> cyc_steps;  // steps of each cycle
     const DevOp op = make_devop(p.op, prm->transpose);
+    ArnoldiSteps steps1(ctx);  // a cycle's steps in one launch, where that applies
+    if (!rc && !pre) rc = steps1.init(op, m, H1, H2, Nd);
     const int maxcyc = prm->max_extra_cycles > 0 ? prm->max_extra_cycles : 1000;
     std::vector<double> h1(hsz), h2(hsz), nrm(m), Hbar(hsz), rhs(m + 1), y(m), res(m + 1);
     SolveState S;
@@ -760,7 +762,8 @@ static int gmres_single(tgdk_ctx ctx, const ProbSpec& p, const tgdk_solve_params
         // this cycle's length (variable restarting), at most m
         const int mc = cyc < prm->n_cycle_lengths && prm->cycle_lengths ? prm->cycle_lengths[cyc] : m;
         int steps = mc;
-        for (int j = 0; j < mc; ++j) {
+        if (steps1.rq && (rc = steps1.run(0, mc, false, V))) break;
+        for (int j = 0; j < mc && !steps1.rq; ++j) {
             if (pre) {  // right preconditioning: w = A M^{-1} v_j
                 if ((rc = prm->precond(prm->precond_user, V + (size_t)j * n, pz, 1))) break;
                 launch_apply<double>(op, pz, w, 1, p.op->tile_id[0], s);
@@ -780,7 +783,7 @@ static int gmres_single(tgdk_ctx ctx, const ProbSpec& p, const tgdk_solve_params
         TGDK_HIP(hipMemcpyAsync(h2.data(), H2, sizeof(double) * hsz, hipMemcpyDeviceToHost, s));
         TGDK_HIP(hipMemcpyAsync(nrm.data(), Nd, sizeof(double) * m, hipMemcpyDeviceToHost, s));
         TGDK_HIP(hipMemcpyAsync(&S, g.d_states, sizeof(SolveState), hipMemcpyDeviceToHost, s));
-        TGDK_HIP(hipStreamSynchronize(s));
+        if ((rc = steps1.wait())) break;
         // Hbar (row-major (m+1) x m); stop at an exact zero subdiagonal
         std::fill(Hbar.begin(), Hbar.end(), 0.0);
         for (int j = 0; j < mc; ++j) {
@@ -811,6 +814,7 @@ static int gmres_single(tgdk_ctx ctx, const ProbSpec& p, const tgdk_solve_params
         TGDK_HIP(hipGetLastError());
         TGDK_HIP(hipStreamSynchronize(s));
     }
+    steps1.release();
     release();
     if (rc) return rc;
     const double secs = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
