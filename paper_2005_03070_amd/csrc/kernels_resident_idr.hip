@@ -14,14 +14,18 @@
 // f = P^T r with ||r||^2.  The s x s solves are taken by one thread of every
 // workgroup, redundantly.
 //
-// s <= 4: 64 x 64 tiles, 8 points a thread (P: 128 KB of LDS in float64); s <=
-// 8: 64 x 32 tiles, 4 points a thread.  Microseconds per operator application
-// (vector kernels -> this kernel): s = 4, float64 127^2 25.7 -> 9.0, 511^2 30.1 ->
-// 10.3, 1023^2 50.7 -> 12.8; float32 511^2 25.2 -> 8.2; s = 1, 511^2 25.1 -> 5.2; s = 8,
-// 511^2 46.1 -> 13.3.  Bound now by the exchanges and by instructions; in float64
-// with s = 4 or 8 about 60 spilled registers a step cost 2 us of them (loads of
-// a stencil and of the products held to two points and one column at a time:
-// 11.8 -> 10.3 us; steps unrolled over the columns spilled more).
+// Tiles are 64 x 16, 32 or 64 (2, 4 or 8 points a thread; P: at most 128 KB of
+// LDS): the smallest that leave at most one per compute unit.  More points a
+// thread run into spills (float64 with 8 points and s = 4, or 4 points and s = 8:
+// 60 registers a step) and instructions issued by too few units; more
+// workgroups cost the exchange little.  Microseconds per operator application
+// with 64 x 64 and 64 x 16 tiles, float64, s = 4: 63^2 6.7 and 4.9, 127^2 9.0 and 5.6,
+// 255^2 10.0 and 6.4, 511^2 10.4 and 6.9; s = 8 with 64 x 32 and 64 x 16: 127^2 11.9 and 8.6,
+// 511^2 13.2 and 10.2; s = 1: 255^2 4.8 and 4.4.  A grid that one workgroup's tile
+// holds without spills takes one (63^2, s = 1: 2.5, in four 3.2).  Vector kernels
+// -> this one, float64, s = 4: 127^2 25.7 -> 5.6, 511^2 30.1 -> 6.9, 1023^2 (64 x 64)
+// 50.7 -> 12.8; s = 1, 511^2 25.1 -> 4.8; s = 8, 511^2 46.1 -> 10.2.  Bound now by the
+// exchanges (2 to 2.6 us) and, at 1023^2 with s = 4, by the spills.
 #include "resident2d.h"
 
 namespace tgdk {
@@ -352,23 +356,40 @@ __global__ __launch_bounds__(RT) void k_resident_idr(ResArgs A, const double* P6
     if (leader) res_end(S, st, mvps, inner);
 }
 
-template <bool VAR, class TI>
-static const void* idr_kernel(int s) {
-    if (s <= 1) return (const void*)k_resident_idr<VAR, TI, 1, 8>;
-    if (s <= 2) return (const void*)k_resident_idr<VAR, TI, 2, 8>;
-    if (s <= 4) return (const void*)k_resident_idr<VAR, TI, 4, 8>;
-    return (const void*)k_resident_idr<VAR, TI, 8, 4>;
+template <bool VAR, class TI, int SM>
+static const void* idr_kernel_rows(int rows) {
+    if constexpr (SM <= 4)
+        if (rows == 64) return (const void*)k_resident_idr<VAR, TI, SM, 8>;
+    if (rows == 32) return (const void*)k_resident_idr<VAR, TI, SM, 4>;
+    return (const void*)k_resident_idr<VAR, TI, SM, 2>;
 }
 
-int resident_idr_rows(int s) { return s <= 4 ? 64 : s <= RES_IDR_SMAX ? 32 : 0; }
+template <bool VAR, class TI>
+static const void* idr_kernel(int s, int rows) {
+    if (s <= 1) return idr_kernel_rows<VAR, TI, 1>(rows);
+    if (s <= 2) return idr_kernel_rows<VAR, TI, 2>(rows);
+    if (s <= 4) return idr_kernel_rows<VAR, TI, 4>(rows);
+    return idr_kernel_rows<VAR, TI, 8>(rows);
+}
+
+int resident_idr_rows(int s, const DevOp& op, int max_team) {
+    if (s > RES_IDR_SMAX) return 0;
+    const int one = s <= 2 ? 64 : s <= 4 ? 32 : 16;  // rows of a tile whose vectors don't spill
+    for (int rows = 16; rows <= (s <= 4 ? 64 : 32); rows *= 2) {
+        const long long tiles = (long long)((op.nx + RTILE - 1) / RTILE) * ((op.ny + rows - 1) / rows);
+        const bool fits = op.nx <= RTILE && op.ny <= one;  // one workgroup, no exchange
+        if (tiles <= (fits ? 1 : max_team)) return rows;
+    }
+    return 0;
+}
 
 hipError_t launch_resident_idr(int inner_f32, int var, const ResArgs& args, const DevProb* prob, const double* P64,
-                               int s, double kappa, hipStream_t stream) {
+                               int s, int rows, double kappa, hipStream_t stream) {
     launch_res_setup(args, prob, 1, stream);
     ResArgs a = args;
     void* av[] = {&a, &P64, &s, &kappa};
-    const void* f = inner_f32 ? (var ? idr_kernel<true, float>(s) : idr_kernel<false, float>(s))
-                              : (var ? idr_kernel<true, double>(s) : idr_kernel<false, double>(s));
+    const void* f = inner_f32 ? (var ? idr_kernel<true, float>(s, rows) : idr_kernel<false, float>(s, rows))
+                              : (var ? idr_kernel<true, double>(s, rows) : idr_kernel<false, double>(s, rows));
     return hipLaunchCooperativeKernel(f, dim3(args.team), dim3(RT), av, 0, stream);
 }
 

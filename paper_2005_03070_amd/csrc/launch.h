@@ -55,11 +55,11 @@ hipError_t launch_resident2d(int inner_f32, int var, const ResArgs& args, const 
                              hipStream_t s);
 void launch_res_setup(const ResArgs& args, const DevProb* probs, int teams, hipStream_t s);
 // The same for one IDR(s) solve (P64: the s orthonormal shadow columns);
-// resident_idr_rows: grid rows of a tile for s (0: s too large).
+// resident_idr_rows: grid rows of a tile (0: s too large, or more tiles than max_team).
 constexpr int RES_IDR_SMAX = 8;
-int resident_idr_rows(int s);
+int resident_idr_rows(int s, const DevOp& op, int max_team);
 hipError_t launch_resident_idr(int inner_f32, int var, const ResArgs& args, const DevProb* prob, const double* P64,
-                               int s, double kappa, hipStream_t stream);
+                               int s, int rows, double kappa, hipStream_t stream);
 
 // Arnoldi steps j0 .. j1 - 1 on a 2-D grid in one launch: column j of V
 // multiplied by A, orthogonalised twice against columns 0 .. j (coefficients

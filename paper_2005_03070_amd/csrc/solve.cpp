@@ -196,13 +196,13 @@ struct ExtWs {
 // Up to that size it is faster everywhere: 63^2 (one tile) 14.9 -> 3.1 us per
 // iteration, 1023^2 (256 tiles) 31.8 -> 7.5 us; beyond it the tiles do not fit.
 // With the measurement of single step launches on, the step kernel runs.
-// IDR(s) has the same scheme for s <= 8 without a preconditioner (idr_s; 64 x
-// 32 tiles past s = 4): 511^2 with s = 4 30 -> 10 us per operator application.
+// IDR(s) has the same scheme for s <= 8 without a preconditioner (idr_s, tiles
+// of 16 to 64 rows): 511^2 with s = 4 30 -> 7 us per operator application.
 static int resident_team(tgdk_ctx ctx, const std::vector<ProbSpec>& ps, const tgdk_solve_params* prm, int idr_s) {
     if (ps[0].op->dim != 2) return 0;
     int rows = RES_TILE;
     if (prm->method == TGDK_IDRS_PROJ) {
-        rows = prm->precond ? 0 : resident_idr_rows(idr_s);
+        rows = prm->precond ? 0 : resident_idr_rows(idr_s, make_devop(ps[0].op, 0), std::min(ctx->num_cus, 256));
         if (rows == 0) return 0;
     } else if (prm->method != TGDK_BICGSTAB_PROJ || ctx->time_which) {
         return 0;
@@ -624,7 +624,8 @@ static int resident_group(Group& g, const std::vector<ProbSpec>& ps, tgdk_solve_
     tgdk_ctx ctx = g.ctx;
     hipStream_t s = ctx->stream;
     if (idr_s > 0)
-        TGDK_HIP(launch_resident_idr(g.inner_f32, g.var, g.res, g.probs.data(), P64, idr_s, kappa, s));
+        TGDK_HIP(launch_resident_idr(g.inner_f32, g.var, g.res, g.probs.data(), P64, idr_s,
+                                     resident_idr_rows(idr_s, g.probs[0].op, std::min(ctx->num_cus, 256)), kappa, s));
     else
         TGDK_HIP(launch_resident2d(g.inner_f32, g.var, g.res, g.probs.data(), g.teams, s));
     TGDK_HIP(hipEventRecord(ctx->events[0], s));

@@ -150,3 +150,19 @@ def test_idr_tile_edges(dims, s):
     if s not in (3, 8):
         xs = ODS.solve(oop, b, transpose=transpose)
         assert np.linalg.norm(x.cpu().numpy() - xs) <= 1.02e-9 * np.linalg.norm(b) / _lambda(dims)
+
+
+# tiles of 16, 32 and 64 rows: one workgroup with and without spills, the
+# most tiles of a height and one row more
+@pytest.mark.parametrize("dims,s", [((64, 64), 2), ((64, 65), 2), ((63, 32), 4), ((63, 33), 4), ((64, 16), 8),
+                                    ((64, 17), 8), ((1024, 256), 4), ((1024, 257), 4), ((1024, 513), 4),
+                                    ((1024, 257), 8)])
+def test_idr_tile_heights(dims, s):
+    n = dims[0] * dims[1]
+    oop, op = O.const_cd(dims, (6.0, 3.0)), tg().Operator.const_cd(dims, (6.0, 3.0), device=DEV)
+    b = W.rhs(n, 23)
+    shadow = torch.tensor(W.shadow_draw(n, s, 9), device=DEV)
+    x, rep = tg().solve_idr(op, torch.tensor(b, device=DEV), s=s, shadow=shadow, rtol=1e-9, max_extra=200)
+    r = b - O.apply(oop, x.cpu().numpy())
+    assert rep.status == 0 and np.linalg.norm(r) <= 1.01e-9 * np.linalg.norm(b)
+    assert rep.mvp_inner == sum(rep.cycle_mvps)
