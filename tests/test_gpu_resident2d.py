@@ -46,6 +46,9 @@ DIMS = [(1, 1), (63, 64), (64, 64), (65, 64), (64, 65), (3, 200), (200, 3), (130
 def test_tile_edges(dims, precision, k, x0):
     if precision == "fp32_ir" and dims == (2112, 40):
         pytest.skip("float32 inner cycles diverge on this grid (h_y / h_x = 52) in the step kernel as well")
+    if precision == "fp32_ir" and dims == (1024, 1024):
+        pytest.skip("whether float32 inner cycles with three vectors converge here depends on rounding (5 of 12 "
+                    "scalings of b in the step kernel, 10 of 12 in this one)")
     n = dims[0] * dims[1]
     k = min(k, n)
     if n == 1 and k:
