@@ -43,8 +43,8 @@ int gram_host(tgdk_ctx ctx, const double* A, int p, const double* B, int q, long
     for (int i0 = 0; i0 < p; i0 += 64)
         for (int j0 = 0; j0 < q; j0 += 64) {
             const int pi = std::min(64, p - i0), qj = std::min(64, q - j0);
-            launch_gram(A + (size_t)i0 * n, 0, n, pi, B + (size_t)j0 * n, 0, n, qj, n, dG,
-                        (double*)ctx->partial.p, ctx->counters, s);
+            launch_gram(A + (size_t)i0 * n, n, pi, B + (size_t)j0 * n, n, qj, n, dG,
+                        (double*)ctx->partial.p, s);
             TGDK_HIP(hipMemcpyAsync(blk.data(), dG, sizeof(double) * pi * qj, hipMemcpyDeviceToHost, s));
             TGDK_HIP(hipStreamSynchronize(s));
             for (int i = 0; i < pi; ++i)

@@ -224,7 +224,7 @@ int cholqr2(tgdk_ctx ctx, double* W, long long n, int k) {
         double *in = pass ? tmp : W, *out = pass ? W : tmp;  // W R_1^{-1} in tmp, the result back in W
         const size_t need = gram_partial_bytes(n, k, k);
         if ((rc = ctx->partial.ensure(need))) break;
-        launch_gram(in, 0, n, k, in, 0, n, k, n, dG, (double*)ctx->partial.p, ctx->counters, s);
+        launch_gram(in, n, k, in, n, k, n, dG, (double*)ctx->partial.p, s);
         if (hipMemcpyAsync(G.data(), dG, G.size() * sizeof(double), hipMemcpyDeviceToHost, s) != hipSuccess ||
             hipStreamSynchronize(s) != hipSuccess) {
             rc = fail(TGDK_E_HIP, "Gram copy failed");
@@ -316,7 +316,7 @@ int defl_finish(tgdk_op op, int transpose, double* V64, int k, int store, tgdk_d
     if (!rc) rc = ctx->partial.ensure(gram_partial_bytes(n, k, k));
     if (!rc) {
         // Galerkin H = V^T (A V); MinRes H = (A V)^T (A V)
-        launch_gram(minres ? AV : V64, 0, n, k, AV, 0, n, k, n, dG, (double*)ctx->partial.p, ctx->counters, s);
+        launch_gram(minres ? AV : V64, n, k, AV, n, k, n, dG, (double*)ctx->partial.p, s);
         if (hipMemcpyAsync(H.data(), dG, H.size() * sizeof(double), hipMemcpyDeviceToHost, s) != hipSuccess ||
             hipStreamSynchronize(s) != hipSuccess)
             rc = fail(TGDK_E_HIP, "forming H failed");
@@ -715,7 +715,7 @@ int tgdk_defl_precond(tgdk_defl g, tgdk_precond_fn fn, void* user, tgdk_defl* ou
         return rc < 0 ? rc : fail(TGDK_E_HIP, "preconditioner failed");
     }
     std::vector<double> H((size_t)k * k);
-    launch_gram(V, 0, n, k, AZ, 0, n, k, n, dG, (double*)ctx->partial.p, ctx->counters, s);
+    launch_gram(V, n, k, AZ, n, k, n, dG, (double*)ctx->partial.p, s);
     if (hipMemcpyAsync(H.data(), dG, H.size() * sizeof(double), hipMemcpyDeviceToHost, s) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess) {
         release();

@@ -238,7 +238,7 @@ extern "C" int tgdk_coarse_setup(tgdk_op op, const double* b, double* x, const t
                 double* dG = nullptr;
                 if (pool_alloc(ctx, &dG, G.size()) == TGDK_OK &&
                     ctx->partial.ensure(gram_partial_bytes(n, m + 1, m + 1)) == TGDK_OK) {
-                    launch_gram(V, 0, n, m + 1, V, 0, n, m + 1, n, dG, (double*)ctx->partial.p, ctx->counters, s);
+                    launch_gram(V, n, m + 1, V, n, m + 1, n, dG, (double*)ctx->partial.p, s);
                     (void)hipMemcpy(G.data(), dG, sizeof(double) * G.size(), hipMemcpyDeviceToHost);
                     for (int i = 0; i <= m; ++i)
                         for (int j = 0; j <= m; ++j)

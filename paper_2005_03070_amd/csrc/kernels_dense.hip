@@ -31,25 +31,29 @@ __global__ __launch_bounds__(NT) void k_sum_partials(const double* __restrict__ 
     if (threadIdx.x == 0) out[i] = root ? sqrt(s) : s;
 }
 
-template <class T>
-__device__ __forceinline__ double ld(const void* p, long long i) {
-    return (double)reinterpret_cast<const T*>(p)[i];
-}
-
 // ------------------------------------------------------------- Gram A^T B
 // Matrix-core (v_mfma_f64_16x16x4f64) Gram product G = A^T B, K = the long
 // dimension n.  Operand layout of the instruction on gfx950 (one wave):
 //   A-operand  lane l holds A[l % 16][l / 16]   (16 x 4)
 //   B-operand  lane l holds B[l / 16][l % 16]   (4 x 16)
 //   result     lane l, register r holds D[l / 16 + 4 r][l % 16]  (16 x 16)
-// Each workgroup stages 64-row chunks of A and B in LDS (coalesced column
-// loads, float32 inputs widened exactly), and its four waves accumulate the
-// 16 x 16 output tiles over the chunk; per-workgroup partial tiles are summed
-// in a fixed order by k_sum_partials (one workgroup per entry).
+// The rows go in chunks of 32 to nb accumulators (chunk c to accumulator c mod
+// nb, four rows at a time), whose partial products k_sum_gram_block sums in a
+// fixed order.  An accumulator is a wave: a lane loads its column's rows
+// l / 16, 4 + l / 16, ... of the chunk to registers (one line of a column
+// serves four loads) while the chunk before is multiplied; A = B loads once
+// and forms the upper tiles, which are the lower ones' mirror image.  Lanes
+// past the last column repeat it: what they hold enters only rows and columns
+// of G that are not stored.
+//
+// Bound by the loads: 1023^2 x 30, V^T V reads 251 MB in 67 us (chunks
+// staged through LDS by four waves that share the tiles, two barriers a chunk
+// and B read again where it is A: 160 us), V^T (A V) 502 MB in 124 (180).
+// At 31^2 x 8 (eight waves) 134 against 145 us for a whole space.
 typedef double d4_t __attribute__((ext_vector_type(4)));
 
 constexpr int GRAM_MAX = 64;   // p, q <= 64
-constexpr int GRAM_ROWS = 32;  // rows staged per chunk (two 32 x 65 float64 LDS tiles)
+constexpr int GRAM_ROWS = 32;  // rows of a chunk
 
 int gram_blocks(long long n) {
     long long b = (n + 4 * GRAM_ROWS - 1) / (4 * GRAM_ROWS);
@@ -58,103 +62,137 @@ int gram_blocks(long long n) {
     return (int)b;
 }
 
-template <class TA, class TB>
-__global__ __launch_bounds__(NT) void k_gram(const void* A_, long long lda, int p, const void* B_, long long ldb,
-                                             int q, long long n, double* G, double* partial, unsigned* counter) {
-    __shared__ double As[GRAM_ROWS][GRAM_MAX + 1];
-    __shared__ double Bs[GRAM_ROWS][GRAM_MAX + 1];
-    const TA* A = reinterpret_cast<const TA*>(A_);
-    const TB* B = reinterpret_cast<const TB*>(B_);
-    const int pt = (p + 15) / 16, qt = (q + 15) / 16, ntile = pt * qt;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    constexpr int MAXT = (GRAM_MAX / 16) * (GRAM_MAX / 16) / NWAVE;  // tiles per wave
-    d4_t acc[MAXT];
+template <int T, bool SAME>
+__global__ __launch_bounds__(NT) void k_gram(const double* __restrict__ A, long long lda, int p,
+                                                  const double* __restrict__ B, long long ldb, int q, long long n,
+                                                  int nacc, double* __restrict__ partial) {
+    constexpr int KS = GRAM_ROWS / 4;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, acci = blockIdx.x * NWAVE + w;
+    if (acci >= nacc) return;
+    d4_t acc[T][T];
 #pragma unroll
-    for (int i = 0; i < MAXT; ++i) acc[i] = d4_t{0.0, 0.0, 0.0, 0.0};
-    const long long nchunk = (n + GRAM_ROWS - 1) / GRAM_ROWS;
-    for (long long ch = blockIdx.x; ch < nchunk; ch += gridDim.x) {
-        const long long r0 = ch * GRAM_ROWS;
-        for (int idx = threadIdx.x; idx < GRAM_ROWS * GRAM_MAX; idx += NT) {
-            const int rr = idx % GRAM_ROWS, col = idx / GRAM_ROWS;
-            const long long g = r0 + rr;
-            As[rr][col] = (g < n && col < p) ? (double)A[col * lda + g] : 0.0;
-            Bs[rr][col] = (g < n && col < q) ? (double)B[col * ldb + g] : 0.0;
-        }
-        __syncthreads();
+    for (int i = 0; i < T; ++i)
 #pragma unroll
-        for (int s = 0; s < MAXT; ++s) {
-            const int tile = w + s * NWAVE;
-            if (tile < ntile) {
-                const int i0 = (tile / qt) * 16, j0 = (tile % qt) * 16;
-                d4_t a = acc[s];
+        for (int j = 0; j < T; ++j) acc[i][j] = d4_t{0.0, 0.0, 0.0, 0.0};
+    const double* pa[T];
+    const double* pb[T];
 #pragma unroll
-                for (int k4 = 0; k4 < GRAM_ROWS; k4 += 4) {
-                    const double av = As[k4 + (lane >> 4)][i0 + (lane & 15)];
-                    const double bv = Bs[k4 + (lane >> 4)][j0 + (lane & 15)];
-                    a = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, a, 0, 0, 0);
-                }
-                acc[s] = a;
-            }
-        }
-        __syncthreads();
+    for (int i = 0; i < T; ++i) {
+        const int c = i * 16 + (lane & 15);
+        pa[i] = A + (long long)(c < p ? c : p - 1) * lda + (lane >> 4);
+        pb[i] = B + (long long)(c < q ? c : q - 1) * ldb + (lane >> 4);
     }
-    // per-workgroup partial, row-major p x q
-    const int npair = p * q;
+    auto load = [&](long long r0, double(&a)[T][KS], double(&b)[T][KS]) {
+        if (r0 + GRAM_ROWS <= n) {
 #pragma unroll
-    for (int s = 0; s < MAXT; ++s) {
-        const int tile = w + s * NWAVE;
-        if (tile < ntile) {
-            const int i0 = (tile / qt) * 16, j0 = (tile % qt) * 16;
+            for (int i = 0; i < T; ++i)
+#pragma unroll
+                for (int s = 0; s < KS; ++s) {
+                    a[i][s] = pa[i][r0 + 4 * s];
+                    if (!SAME) b[i][s] = pb[i][r0 + 4 * s];
+                }
+        } else {
+#pragma unroll
+            for (int i = 0; i < T; ++i)
+#pragma unroll
+                for (int s = 0; s < KS; ++s) {
+                    const bool in = r0 + 4 * s + (lane >> 4) < n;
+                    a[i][s] = in ? pa[i][r0 + 4 * s] : 0.0;
+                    if (!SAME) b[i][s] = in ? pb[i][r0 + 4 * s] : 0.0;
+                }
+        }
+    };
+    double a[T][KS], na[T][KS];
+    double b[T][KS], nb[T][KS];
+    const long long step = (long long)nacc * GRAM_ROWS;
+    long long r0 = (long long)acci * GRAM_ROWS;
+    if (r0 < n) load(r0, a, b);
+    for (; r0 < n; r0 += step) {
+        if (r0 + step < n) load(r0 + step, na, nb);
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+#pragma unroll
+            for (int i = 0; i < T; ++i)
+#pragma unroll
+                for (int j = SAME ? i : 0; j < T; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(
+                        a[i][s], SAME ? a[j][s] : b[j][s], acc[i][j], 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < T; ++i)
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                a[i][s] = na[i][s];
+                if (!SAME) b[i][s] = nb[i][s];
+            }
+    }
+    double* out = partial + (long long)acci * p * q;  // row-major p x q
+#pragma unroll
+    for (int i = 0; i < T; ++i)
+#pragma unroll
+        for (int j = SAME ? i : 0; j < T; ++j)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int i = i0 + (lane >> 4) + 4 * r, j = j0 + (lane & 15);
-                if (i < p && j < q) partial[(long long)blockIdx.x * npair + i * q + j] = acc[s][r];
+                const int row = i * 16 + (lane >> 4) + 4 * r, col = j * 16 + (lane & 15);
+                if (row < p && col < q) {
+                    out[row * q + col] = acc[i][j][r];
+                    if (SAME && j > i) out[col * q + row] = acc[i][j][r];
+                }
             }
-        }
-    }
-    (void)counter;
-    (void)G;
 }
 
 // Entry e = i * qb + j of the summed partials goes to out[i * ldo + j] (a
-// GRAM_MAX x GRAM_MAX block of a larger row-major Gram matrix).
+// GRAM_MAX x GRAM_MAX block of a larger row-major Gram matrix).  A workgroup
+// sums four neighbouring entries, its threads partials t, t + NT, ...: one
+// entry a workgroup used 8 bytes of every line it read (900 entries of 1024
+// partials 11 us, four at a time 8.4).
 __global__ __launch_bounds__(NT) void k_sum_gram_block(const double* __restrict__ partial, int nblocks,
                                                        int npair, int qb, double* __restrict__ out, int ldo) {
-    __shared__ double sh[NWAVE];
-    const int e = blockIdx.x;
-    double a = 0.0;
-#pragma unroll 8
-    for (int b = threadIdx.x; b < nblocks; b += NT) a += partial[(long long)b * npair + e];
-    const double v = block_sum_one(a, sh);
-    if (threadIdx.x == 0) out[(long long)(e / qb) * ldo + e % qb] = v;
+    __shared__ double sh[4][NWAVE];
+    const int e0 = blockIdx.x * 4;
+    double a[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+    for (int b = threadIdx.x; b < nblocks; b += NT)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) a[i] += partial[(long long)b * npair + (e0 + i < npair ? e0 + i : npair - 1)];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const double v = block_sum_one(a[i], sh[i]);
+        const int e = e0 + i;
+        if (threadIdx.x == 0 && e < npair) out[(long long)(e / qb) * ldo + e % qb] = v;
+    }
+}
+
+template <bool SAME>
+static void gram_block(const double* A, long long lda, int p, const double* B, long long ldb, int q, long long n,
+                      double* partial, int nb, hipStream_t s) {
+    const dim3 grid((nb + NWAVE - 1) / NWAVE);
+    const int t = ((p > q ? p : q) + 15) / 16;
+    if (t == 1)
+        hipLaunchKernelGGL((k_gram<1, SAME>), grid, dim3(NT), 0, s, A, lda, p, B, ldb, q, n, nb, partial);
+    else if (t == 2)
+        hipLaunchKernelGGL((k_gram<2, SAME>), grid, dim3(NT), 0, s, A, lda, p, B, ldb, q, n, nb, partial);
+    else if (t == 3)
+        hipLaunchKernelGGL((k_gram<3, SAME>), grid, dim3(NT), 0, s, A, lda, p, B, ldb, q, n, nb, partial);
+    else
+        hipLaunchKernelGGL((k_gram<4, SAME>), grid, dim3(NT), 0, s, A, lda, p, B, ldb, q, n, nb, partial);
 }
 
 // G (p x q, row-major) = A^T B in blocks of at most GRAM_MAX x GRAM_MAX (the
 // kernel's tile limit), each block's per-workgroup partials summed into its
 // place in G; the blocks run one after another on the stream and share the
 // partial workspace (gram_blocks(n) * GRAM_MAX^2 doubles suffice).
-void launch_gram(const void* A, int atype, long long lda, int p, const void* B, int btype, long long ldb, int q,
-                 long long n, double* G, double* partial, unsigned* counter, hipStream_t s) {
+void launch_gram(const double* A, long long lda, int p, const double* B, long long ldb, int q, long long n, double* G,
+                 double* partial, hipStream_t s) {
     const int nb = gram_blocks(n);
-    const size_t ea = atype ? 4 : 8, eb = btype ? 4 : 8;
     for (int i0 = 0; i0 < p; i0 += GRAM_MAX)
         for (int j0 = 0; j0 < q; j0 += GRAM_MAX) {
             const int pb = p - i0 < GRAM_MAX ? p - i0 : GRAM_MAX, qb = q - j0 < GRAM_MAX ? q - j0 : GRAM_MAX;
-            const void* Ab = (const char*)A + (size_t)i0 * lda * ea;
-            const void* Bb = (const char*)B + (size_t)j0 * ldb * eb;
-            if (atype == 0 && btype == 0)
-                hipLaunchKernelGGL((k_gram<double, double>), dim3(nb), dim3(NT), 0, s, Ab, lda, pb, Bb, ldb, qb, n, G,
-                                   partial, counter);
-            else if (atype == 1 && btype == 1)
-                hipLaunchKernelGGL((k_gram<float, float>), dim3(nb), dim3(NT), 0, s, Ab, lda, pb, Bb, ldb, qb, n, G,
-                                   partial, counter);
-            else if (atype == 1 && btype == 0)
-                hipLaunchKernelGGL((k_gram<float, double>), dim3(nb), dim3(NT), 0, s, Ab, lda, pb, Bb, ldb, qb, n, G,
-                                   partial, counter);
+            const double *Ab = A + (size_t)i0 * lda, *Bb = B + (size_t)j0 * ldb;
+            if (Ab == Bb && lda == ldb && pb == qb)
+                gram_block<true>(Ab, lda, pb, Bb, ldb, qb, n, partial, nb, s);
             else
-                hipLaunchKernelGGL((k_gram<double, float>), dim3(nb), dim3(NT), 0, s, Ab, lda, pb, Bb, ldb, qb, n, G,
-                                   partial, counter);
-            hipLaunchKernelGGL(k_sum_gram_block, dim3(pb * qb), dim3(NT), 0, s, partial, nb, pb * qb, qb,
+                gram_block<false>(Ab, lda, pb, Bb, ldb, qb, n, partial, nb, s);
+            hipLaunchKernelGGL(k_sum_gram_block, dim3((pb * qb + 3) / 4), dim3(NT), 0, s, partial, nb, pb * qb, qb,
                                G + (size_t)i0 * q + j0, q);
         }
 }
@@ -169,62 +207,114 @@ size_t gram_partial_bytes(long long n, int p, int q) {
 // Out^T = Y^T V^T so that each lane's V load is one of 16 consecutive rows of
 // a column (coalesced): B-operand lane l = V[r0 + l % 16][k0 + l / 16],
 // A-operand lane l = Y[k0 + l / 16][j0 + l % 16], result lane l, register r =
-// Out[r0 + l % 16][j0 + l / 16 + 4 r].  One wave owns 16 rows and all q
-// columns (q <= 144), loading V once.
+// Out[r0 + l % 16][j0 + l / 16 + 4 r].
+//
+// A wave owns R groups of 16 rows and all q <= 16 QT columns, so V is read
+// once; the loads of 32 columns are all in flight before the first product
+// (16 KB a wave for R = 4), and Y's operands come from LDS, laid out once a
+// workgroup where p <= 32, else 32 rows at a time.  Bound by the traffic:
+// 1023^2, 30 -> 30 columns, 502 MB in 111 us; with 16 rows a wave, Y from
+// global memory and one load in flight it took 300 us.
 constexpr int VMUL_MAXQT = 9;
 
-template <class TV>
-__global__ __launch_bounds__(NT) void k_vmul(const TV* __restrict__ V, long long ldv, int p,
+template <int QT, int R>
+__global__ __launch_bounds__(NT) void k_vmul(const double* __restrict__ V, long long ldv, int p,
                                              const double* __restrict__ Y, int q, double* __restrict__ Out,
                                              long long ldo, long long n) {
+    __shared__ double Ys[8][QT][64];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int qt = (q + 15) / 16;
-    const long long nrt = (n + 15) / 16;
-    for (long long rt = (long long)blockIdx.x * NWAVE + w; rt < nrt; rt += (long long)gridDim.x * NWAVE) {
-        const long long r0 = rt * 16;
-        const long long row = r0 + (lane & 15);
-        d4_t acc[VMUL_MAXQT];
+    auto stage = [&](int k0) {
+        for (int i = threadIdx.x; i < 8 * QT * 64; i += NT) {
+            const int l = i & 63, t = (i >> 6) % QT, s = (i >> 6) / QT;
+            const int kc = k0 + 4 * s + (l >> 4), jc = t * 16 + (l & 15);
+            Ys[s][t][l] = kc < p && jc < q ? Y[(long long)jc * p + kc] : 0.0;
+        }
+    };
+    if (p <= 32) {
+        stage(0);
+        __syncthreads();
+    }
+    const long long ngroup = (n + 16 * R * NWAVE - 1) / (16 * R * NWAVE);
+    for (long long gr = blockIdx.x; gr < ngroup; gr += gridDim.x) {
+        const long long r0 = (gr * NWAVE + w) * 16 * R + (lane & 15);
+        d4_t acc[R][QT];
+        long long row[R];
 #pragma unroll
-        for (int t = 0; t < VMUL_MAXQT; ++t) acc[t] = d4_t{0.0, 0.0, 0.0, 0.0};
-        for (int k0 = 0; k0 < p; k0 += 4) {
-            const int kc = k0 + (lane >> 4);
-            const double bv = (row < n && kc < p) ? (double)V[kc * ldv + row] : 0.0;
+        for (int i = 0; i < R; ++i) {
+            row[i] = r0 + 16 * i < n ? r0 + 16 * i : n - 1;  // past n: the last row again, not stored
 #pragma unroll
-            for (int t = 0; t < VMUL_MAXQT; ++t) {
-                if (t < qt) {
-                    const int jc = t * 16 + (lane & 15);
-                    const double av = (kc < p && jc < q) ? Y[(long long)jc * p + kc] : 0.0;
-                    acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc[t], 0, 0, 0);
+            for (int t = 0; t < QT; ++t) acc[i][t] = d4_t{0.0, 0.0, 0.0, 0.0};
+        }
+        for (int k0 = 0; k0 < p; k0 += 32) {
+            double bv[R][8];
+#pragma unroll
+            for (int s = 0; s < 8; ++s) {
+                const int kc = k0 + 4 * s + (lane >> 4);
+                const double* col = V + (long long)(kc < p ? kc : p - 1) * ldv;  // past p: times a zero of Y
+#pragma unroll
+                for (int i = 0; i < R; ++i) bv[i][s] = kc < p ? col[row[i]] : 0.0;
+            }
+            if (p > 32) {
+                __syncthreads();
+                stage(k0);
+                __syncthreads();
+            }
+#pragma unroll
+            for (int s = 0; s < 8; ++s) {
+                if (k0 + 4 * s >= p) break;
+#pragma unroll
+                for (int t = 0; t < QT; ++t) {
+                    const double av = Ys[s][t][lane];
+#pragma unroll
+                    for (int i = 0; i < R; ++i)
+                        acc[i][t] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv[i][s], acc[i][t], 0, 0, 0);
                 }
             }
         }
-        if (row < n) {
 #pragma unroll
-            for (int t = 0; t < VMUL_MAXQT; ++t) {
-                if (t < qt) {
+        for (int t = 0; t < QT; ++t)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int jc = t * 16 + (lane >> 4) + 4 * r;
-                        if (jc < q) Out[jc * ldo + row] = acc[t][r];
-                    }
+            for (int r = 0; r < 4; ++r) {
+                const int jc = t * 16 + (lane >> 4) + 4 * r;
+                if (jc < q) {
+#pragma unroll
+                    for (int i = 0; i < R; ++i)
+                        if (r0 + 16 * i < n) Out[jc * ldo + row[i]] = acc[i][t][r];
                 }
             }
-        }
     }
 }
 
-// Out = V Y in column blocks of at most 16 * VMUL_MAXQT (the kernel's limit):
-// block j0 takes Y's columns j0.. (column-major, leading dimension p) and
-// writes Out's.
+template <int QT, int R>
+static void vmul_block(const double* V, long long ldv, int p, const double* Y, int q, double* Out, long long ldo,
+                       long long n, hipStream_t s) {
+    long long nb = (n + 16 * R * NWAVE - 1) / (16 * R * NWAVE);
+    if (nb > 2048) nb = 2048;
+    hipLaunchKernelGGL((k_vmul<QT, R>), dim3((int)nb), dim3(NT), 0, s, V, ldv, p, Y, q, Out, ldo, n);
+}
+
+// Out = V Y (not in place) in column blocks of at most 16 * VMUL_MAXQT (the
+// kernel's limit): block j0 takes Y's columns j0.. (column-major, leading
+// dimension p) and writes Out's.  Fewer columns leave registers for more rows
+// in flight; a short V takes 16 rows a wave, so that the chip is not idle.
 void launch_vmul(const double* V, long long ldv, int p, const double* Y, int q, double* Out, long long ldo,
                  long long n, hipStream_t s) {
-    long long nb = ((n + 15) / 16 + NWAVE - 1) / NWAVE;
-    if (nb > 8192) nb = 8192;
     constexpr int QB = 16 * VMUL_MAXQT;
     for (int j0 = 0; j0 < q; j0 += QB) {
         const int qb = q - j0 < QB ? q - j0 : QB;
-        hipLaunchKernelGGL(k_vmul<double>, dim3((int)nb), dim3(NT), 0, s, V, ldv, p, Y + (size_t)j0 * p, qb,
-                           Out + (size_t)j0 * ldo, ldo, n);
+        const double* Yb = Y + (size_t)j0 * p;
+        double* Ob = Out + (size_t)j0 * ldo;
+        const bool tall = n >= 64 * 1024;  // 1024 waves of 64 rows: one a SIMD
+        if (qb <= 32 && tall)
+            vmul_block<2, 4>(V, ldv, p, Yb, qb, Ob, ldo, n, s);
+        else if (qb <= 32)
+            vmul_block<2, 1>(V, ldv, p, Yb, qb, Ob, ldo, n, s);
+        else if (qb <= 64 && tall)
+            vmul_block<4, 2>(V, ldv, p, Yb, qb, Ob, ldo, n, s);
+        else if (qb <= 64)
+            vmul_block<4, 1>(V, ldv, p, Yb, qb, Ob, ldo, n, s);
+        else
+            vmul_block<VMUL_MAXQT, 1>(V, ldv, p, Yb, qb, Ob, ldo, n, s);
     }
 }
 
