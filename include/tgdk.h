@@ -92,7 +92,8 @@ int tgdk_ctx_num_cus(tgdk_ctx ctx);
  *  on = 1: durations from the device's constant-rate wall clock, last end
  *          minus first start of the first problem's workgroups;
  *  on = 0: off.
- * Every call clears the totals.  tgdk_ctx_kernel_time returns, for one action
+ * With the hook on the step kernel also solves 2-D systems that otherwise run
+ * in one launch.  Every call clears the totals.  tgdk_ctx_kernel_time returns, for one action
  * (TGDK_STEP_*), the summed duration in ms of the launches in which the first
  * problem did it and their number; TGDK_STEP_ANY sums the launches in which it
  * did work, TGDK_STEP_ALL every launch (including those queued past the end of

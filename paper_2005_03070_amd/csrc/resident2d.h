@@ -258,6 +258,36 @@ __device__ __forceinline__ void basis_update(ResLds& S, const DevProb& P, const 
     for (int q = 0; q < RQ; ++q) w[q] = ok(q) ? w[q] : 0.0;
 }
 
+// S.y = H^{-1} S.y (column-major, k <= MAXK): 16 lanes a row, 32 rows at a time,
+// 8 consecutive entries a lane in flight.  (A thread a row walked its k entries 16 at a
+// time, a memory latency for each 16: a boundary at 511^2 with 100 columns
+// 138 us, now 135; with 30, 64.8 and 63.9.)
+__device__ __forceinline__ void hinv_apply(ResLds& S, const double* __restrict__ h, int k) {
+    const int t = threadIdx.x, lane = t & 15;
+    double* out = S.sh;  // k values, free between exchanges
+    for (int row = t >> 4; row < k; row += 32) {
+        double d = 0.0;
+        for (int j0 = 0; j0 < k; j0 += 128) {
+            double hv[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int j = j0 + 8 * lane + i;
+                hv[i] = h[(j < k ? j : k - 1) * k + row];
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int j = j0 + 8 * lane + i;
+                d += j < k ? hv[i] * S.y[j < k ? j : 0] : 0.0;
+            }
+        }
+        d = row_sum(d);
+        if (lane == 0) out[row] = d;
+    }
+    __syncthreads();
+    if (t < k) S.y[t] = out[t];
+    __syncthreads();
+}
+
 // Start of an inner cycle (all lanes of wave 0): the tolerance of
 // cycle_tolerance with its two powers taken side by side by even and odd
 // lanes, and fresh scalars.
@@ -463,21 +493,7 @@ __device__ __forceinline__ int res_boundary(ResTeam& M, ResLds& S, const ResArgs
             __syncthreads();
             if (S.dead) return -1;
         }
-        double d = 0.0;
-        if (t < k) {
-            // 16 entries of a row of H^{-1} in flight (past k: the last one again, masked)
-            const double* hi = P.hinv + t;
-            for (int j0 = 0; j0 < k; j0 += 16) {
-                double hv[16];
-#pragma unroll
-                for (int j = 0; j < 16; ++j) hv[j] = hi[(j0 + j < k ? j0 + j : k - 1) * k];
-#pragma unroll
-                for (int j = 0; j < 16; ++j) d += j0 + j < k ? hv[j] * S.y[j0 + j < k ? j0 + j : 0] : 0.0;
-            }
-        }
-        __syncthreads();
-        if (t < k) S.y[t] = d;
-        __syncthreads();
+        hinv_apply(S, P.hinv, k);
         double w[RQ];
         auto okq = [&](int q) { return tl.ok(q); };
         if (P.vtype)

@@ -2,7 +2,8 @@
 // (right-hand sides sharing an operator, or independent grid instances) and
 // GMRES(m)-Proj(k) for one right-hand side.
 //
-// BiCGStab: the host only enqueues step launches; every scalar decision
+// 2-D systems that fit the chip run as one cooperative launch (resident_team).
+// BiCGStab otherwise: the host only enqueues step launches; every scalar decision
 // (alpha, omega, cycle tolerance, convergence, breakdown, projection) is
 // taken on the device by the step kernel.  The host watches a host-mapped
 // status mirror one batch behind, so the GPU queue never drains while it
