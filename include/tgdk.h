@@ -463,10 +463,10 @@ int tgdk_solve_noalloc(tgdk_op fine, tgdk_defl defl, const double* b, double* x,
 
 /* Several independent instances (each its own operator, deflation space or
  * NULL, right-hand side and solution, all on the context ctx -- every
- * operator must belong to it -- and of one dimension) solved together:
- * every kernel launch covers the tiles of all instances, so small and uneven
- * grids fill the device in one launch per step.  BiCGStab(ncyc)-Proj(k)
- * only.  Same parameters and reports (one per instance) as tgdk_solve;
+ * operator must belong to it -- and of one dimension) solved together, so
+ * that small and uneven grids fill the device: 2-D grids that fit the chip in
+ * launches of instances of similar sizes, the others with every kernel launch
+ * covering the tiles of all of them.  BiCGStab(ncyc)-Proj(k) only.  Same parameters and reports (one per instance) as tgdk_solve;
  * TGDK_E_INVALID for an operator of another context or dimension. */
 int tgdk_solve_instances(tgdk_ctx ctx, int ninst, const tgdk_op* ops, const tgdk_defl* defls,
                          const double* const* b, double* const* x,

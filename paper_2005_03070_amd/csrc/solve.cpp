@@ -14,6 +14,7 @@
 #include <chrono>
 #include <cmath>
 #include <cstring>
+#include <functional>
 #include <string>
 #include <vector>
 
@@ -194,11 +195,17 @@ struct ExtWs {
 // Workgroups per team of the chip-resident solve, or 0 where the step kernel
 // solves the group: BiCGStab on 2-D grids of at most one 64 x 64 tile per
 // compute unit (every workgroup of a team must be resident, one per unit).
-// Up to that size it is faster everywhere: 63^2 (one tile) 14.9 -> 3.1 us per
-// iteration, 1023^2 (256 tiles) 31.8 -> 7.5 us; beyond it the tiles do not fit.
+// Systems of one size are faster so up to that size: 63^2 (one tile) 14.9 ->
+// 3.1 us per iteration, 1023^2 (256 tiles) 31.8 -> 7.5 us; beyond it the tiles
+// do not fit.  A group's teams have the size of its largest system, so systems
+// of different sizes come in several groups (bicgstab_systems).
 // With the measurement of single step launches on, the step kernel runs.
 // IDR(s) has the same scheme for s <= 8 without a preconditioner (idr_s, tiles
 // of 16 to 64 rows): 511^2 with s = 4 30 -> 7 us per operator application.
+static int tile_count(const tgdk_op op, int rows) {
+    return (int)(((op->n[0] + RES_TILE - 1LL) / RES_TILE) * ((op->n[1] + rows - 1LL) / rows));
+}
+
 static int resident_team(tgdk_ctx ctx, const std::vector<ProbSpec>& ps, const tgdk_solve_params* prm, int idr_s) {
     if (ps[0].op->dim != 2) return 0;
     int rows = RES_TILE;
@@ -208,12 +215,9 @@ static int resident_team(tgdk_ctx ctx, const std::vector<ProbSpec>& ps, const tg
     } else if (prm->method != TGDK_BICGSTAB_PROJ || ctx->time_which) {
         return 0;
     }
-    long long team = 0;
-    for (const auto& p : ps) {
-        const long long tx = (p.op->n[0] + RES_TILE - 1) / RES_TILE, ty = (p.op->n[1] + rows - 1) / rows;
-        team = std::max(team, tx * ty);
-    }
-    return team <= std::min(ctx->num_cus, 256) ? (int)team : 0;
+    int team = 0;
+    for (const auto& p : ps) team = std::max(team, tile_count(p.op, rows));
+    return team <= std::min(ctx->num_cus, 256) ? team : 0;
 }
 
 static void set_space(DevProb& P, tgdk_defl d) {
@@ -236,14 +240,8 @@ static int build_group(tgdk_ctx ctx, const std::vector<ProbSpec>& ps, const tgdk
     g.dim = ps[0].op->dim;
     g.inner_f32 = prm->precision == TGDK_FP32_IR ? 1 : 0;
     g.tile_id = ps[0].op->tile_id[g.inner_f32];
-    int vtype = -1;
-    for (const auto& p : ps)
-        if (p.defl) {
-            const int t = p.defl->store == TGDK_F32 ? 1 : 0;
-            if (vtype >= 0 && vtype != t) return fail(TGDK_E_INVALID, "mixed deflation storage types in one group");
-            vtype = t;
-        }
-    g.vtype = vtype < 0 ? 0 : vtype;
+    for (const auto& p : ps)  // (one type: bicgstab_systems refuses others)
+        if (p.defl) g.vtype = p.defl->store == TGDK_F32 ? 1 : 0;
     int ty, tz;
     tile_shape(g.dim, g.tile_id, &ty, &tz);
     const size_t ies = g.inner_f32 ? 4 : 8;
@@ -706,6 +704,100 @@ static int bicgstab_group(tgdk_ctx ctx, const std::vector<ProbSpec>& ps, const t
     return rc;
 }
 
+// The systems of a call in groups that are solved one after another: the ones
+// past one tile per compute unit (the step kernel's) are one group, the others
+// are split by tile count where that is faster.  With one size for all teams a
+// 1023^2 system beside 256 of 127^2 left a single team of 256 workgroups that
+// took them in turn: 490 ms, where the step kernel advances all of them in each
+// launch in 213; in groups 22.  (One 1023^2 and 128 of 63^2: 156, 88 and 15 ms.)
+//
+// Counts between two powers of two stay together, and neighbouring ones are
+// joined where the queue is predicted to end earlier so: an iteration costs 3.1
+// us on one workgroup and about 4.6 + 0.42 log2(T) us on T (5.4, 6.6, 7.0 and 7.5
+// measured for 4, 16, 64 and 256), and a grid needs iterations in proportion to
+// its longer side.  What a system's numbers are does not depend on its group.
+static int bicgstab_systems(tgdk_ctx ctx, const std::vector<ProbSpec>& ps, const tgdk_solve_params* prm,
+                            tgdk_solve_report* reps, const ExtWs* ext = nullptr) {
+    const auto t0 = std::chrono::steady_clock::now();
+    int vtype = -1;
+    for (const auto& p : ps)
+        if (p.defl) {
+            const int t = p.defl->store == TGDK_F32 ? 1 : 0;
+            if (vtype >= 0 && vtype != t) return fail(TGDK_E_INVALID, "mixed deflation storage types in one group");
+            vtype = t;
+        }
+    const int n = (int)ps.size(), units = std::min(ctx->num_cus, 256);
+    std::vector<int> tiles(n), order(n);
+    bool mixed = false;
+    for (int j = 0; j < n; ++j) {
+        tiles[j] = tile_count(ps[j].op, RES_TILE);
+        order[j] = j;
+        mixed = mixed || tiles[j] != tiles[0];
+    }
+    if (!mixed || ps[0].op->dim != 2 || ctx->time_which) return bicgstab_group(ctx, ps, prm, reps, ext);
+    auto side = [&](int j) { return std::max(ps[j].op->n[0], ps[j].op->n[1]); };
+    // 0: more tiles than units; else 1 + ceil(log2(tiles))
+    auto size_class = [&](int j) {
+        if (tiles[j] > units) return 0;
+        int c = 0;
+        while (tiles[j] > (1 << c)) ++c;
+        return c + 1;
+    };
+    constexpr int NCLASS = 10;
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return size_class(a) < size_class(b); });
+    std::vector<int> start(NCLASS + 1, n);  // first position of a class
+    for (int i = n - 1; i >= 0; --i) start[size_class(order[i])] = i;
+    for (int c = NCLASS - 1; c >= 0; --c) start[c] = std::min(start[c], start[c + 1]);
+    // the time of classes [a, b) in one launch: teams of the largest take the
+    // systems in the order of their sides, each the next when it is done
+    std::vector<int> joint;
+    auto queue_time = [&](int a, int b) {
+        joint.assign(order.begin() + start[a], order.begin() + start[b]);
+        if (joint.empty()) return 0.0;
+        std::stable_sort(joint.begin(), joint.end(), [&](int x, int y) { return side(x) > side(y); });
+        int team = 0;
+        for (int j : joint) team = std::max(team, tiles[j]);
+        const double it = team == 1 ? 3.1 : 4.6 + 0.42 * std::log2((double)team);
+        std::vector<double> end((size_t)std::min((int)joint.size(), std::max(1, units / team)), 0.0);
+        auto later = std::greater<double>();
+        for (int j : joint) {  // (a heap with the earliest end on top)
+            std::pop_heap(end.begin(), end.end(), later);
+            end.back() += it * side(j);
+            std::push_heap(end.begin(), end.end(), later);
+        }
+        return *std::max_element(end.begin(), end.end());
+    };
+    std::vector<double> best(NCLASS + 1, 0.0);  // of classes c and up
+    std::vector<int> next(NCLASS + 1, NCLASS);
+    for (int c = NCLASS - 1; c >= 1; --c) {
+        best[c] = INFINITY;
+        for (int e = c + 1; e <= NCLASS; ++e) {
+            const double t = queue_time(c, e) + best[e];
+            if (t < best[c]) {
+                best[c] = t;
+                next[c] = e;
+            }
+        }
+    }
+    next[0] = 1;
+    int rc = TGDK_OK;
+    for (int c = 0; c < NCLASS; c = next[c]) {
+        std::vector<int> part(order.begin() + start[c], order.begin() + start[next[c]]);
+        if (part.empty()) continue;
+        if (c > 0) std::stable_sort(part.begin(), part.end(), [&](int x, int y) { return side(x) > side(y); });
+        std::vector<ProbSpec> gp;
+        for (int j : part) gp.push_back(ps[j]);
+        std::vector<tgdk_solve_report> gr(part.size());
+        const int grc = bicgstab_group(ctx, gp, prm, gr.data(), ext);
+        if (grc < 0 && grc != TGDK_E_NONFINITE) return grc;
+        rc = worst(rc, grc);
+        for (size_t i = 0; i < part.size(); ++i) reps[part[i]] = gr[i];
+    }
+    const double secs = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
+    for (int j = 0; j < n; ++j) reps[j].seconds = secs;
+    return rc;
+}
+
 // GMRES(m)-Proj(k): one right-hand side.  Arnoldi with classical
 // Gram-Schmidt and one full re-orthogonalisation (CGS2), Hessenberg
 // least squares on the host at the end of each cycle.
@@ -1109,7 +1201,7 @@ int tgdk_solve_instances(tgdk_ctx ctx, int ninst, const tgdk_op* ops, const tgdk
         ps[j] = ProbSpec{ops[j], d, b[j], x[j]};
     }
     TGDK_HIP(hipSetDevice(ctx->device));
-    return bicgstab_group(ctx, ps, prm, reports);
+    return bicgstab_systems(ctx, ps, prm, reports);
 }
 
 }  // extern "C"
