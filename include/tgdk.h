@@ -83,6 +83,20 @@ int tgdk_ctx_create(tgdk_ctx* out, int device, void* hip_stream);
 int tgdk_ctx_destroy(tgdk_ctx ctx);
 /* Number of compute units of the context's device (for launch sizing). */
 int tgdk_ctx_num_cus(tgdk_ctx ctx);
+/* 2-D systems of up to one tile per compute unit (BiCGStab; IDR(s) with s <= 8
+ * and no preconditioner; the Arnoldi steps of GMRES and the coarse set-up) are
+ * solved by launches that hold up to every compute unit until the solve (the
+ * restart cycle) ends, so work on other streams waits for it.
+ *  ON:     the default.  Where the units do not come free within a second, or
+ *          the launch is refused, the kernels of OFF run;
+ *  OFF:    one launch per step or vector operation, between which other
+ *          streams' work can run (2 to 5 times slower);
+ *  CLOSED: as ON with the units never free (for tests of that path).
+ * Results agree to rounding. */
+#define TGDK_ONE_LAUNCH_OFF    0
+#define TGDK_ONE_LAUNCH_ON     1
+#define TGDK_ONE_LAUNCH_CLOSED 2
+int tgdk_ctx_one_launch(tgdk_ctx ctx, int mode);
 /* Measurement hook for the BiCGStab step kernel inside tgdk_solve /
  * tgdk_solve_instances (the first 4096 launches of a call): each launch's
  * duration is added to the total of what the group's first problem did in it.

@@ -18,6 +18,7 @@ CONST_CD, VAR_STENCIL, DIV_K = 0, 1, 2
 BICGSTAB_PROJ, GMRES_PROJ, IDRS_PROJ = 0, 1, 2
 PROJ_GALERKIN, PROJ_MINRES = 0, 1
 FP64, FP32_IR = 0, 1
+ONE_LAUNCH_OFF, ONE_LAUNCH_ON, ONE_LAUNCH_CLOSED = 0, 1, 2
 MAX_DEFL = 256
 NHIST = 8
 IDR_SMAX = 32
@@ -89,6 +90,7 @@ SIGNATURES = [
     ("tgdk_ctx_create", I, [PP, I, P]),
     ("tgdk_ctx_destroy", I, [P]),
     ("tgdk_ctx_num_cus", I, [P]),
+    ("tgdk_ctx_one_launch", I, [P, I]),
     ("tgdk_ctx_time_kernel", I, [P, I]),
     ("tgdk_ctx_kernel_time", I, [P, I, DP, C.POINTER(C.c_longlong)]),
     ("tgdk_stream_probe", I, [P, I, I, I, C.POINTER(C.c_int), I, I, DP]),

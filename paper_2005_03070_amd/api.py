@@ -32,6 +32,14 @@ def context(device=None):
     return _CTX[key]
 
 
+def one_launch(mode, device=None):
+    """How the current stream's context solves 2-D systems that fit the chip:
+    True (the default) in launches that hold it until they end, False in one
+    launch per step, between which other streams' work can run (include/tgdk.h,
+    tgdk_ctx_one_launch)."""
+    check(lib().tgdk_ctx_one_launch(context(device)[0], int(mode)))
+
+
 def _ptr(t, dtype=torch.float64, numel=None, what="tensor"):
     if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise TypeError(f"{what} must be a CUDA tensor")

@@ -43,40 +43,48 @@ void DevBuf::release() {
     cap = 0;
 }
 
-int ArnoldiSteps::init(const DevOp& op, int m, double* H1, double* H2, double* nrm) {
+void ArnoldiSteps::init(const DevOp& op, int m, double* H1, double* H2, double* nrm) {
     a_.op = op;
     a_.H1 = H1;
     a_.H2 = H2;
     a_.nrm = nrm;
     a_.ldh = m + 1;
     a_.pmax = m;
-    rq = arnoldi2d_rows(op, m, std::min(ctx_->num_cus, 256), &a_.team);
-    if (!rq) return TGDK_OK;
+    a_.gate0 = one_launch_gate(ctx_);
+    rq_ = ctx_->one_launch == TGDK_ONE_LAUNCH_OFF ? 0 : arnoldi2d_rows(op, m, std::min(ctx_->num_cus, 256), &a_.team);
+    if (!rq_) return;
     char* p = nullptr;
-    const int rc = pool_alloc(ctx_, &p, (size_t)256 + (size_t)arnoldi2d_words(a_.team, a_.pmax) * 8);
-    if (rc) {
-        rq = 0;
-        return rc;
+    if (pool_alloc(ctx_, &p, (size_t)256 + (size_t)arnoldi2d_words(a_.team, a_.pmax) * 8)) {
+        rq_ = 0;
+        return;
     }
     block_ = p;
     a_.ctl = (unsigned*)p;
     a_.xch = p + 256;
-    return TGDK_OK;
 }
 
-int ArnoldiSteps::run(int j0, int j1, bool reorth, double* V) {
+bool ArnoldiSteps::run(int j0, int j1, bool reorth, double* V) {
+    if (!rq_) return false;
     a_.V = V;
     a_.j0 = j0;
     a_.j1 = j1;
     a_.reorth = reorth;
-    TGDK_HIP(launch_arnoldi2d(a_, rq, ctx_->stream));
-    return TGDK_OK;
+    queued_ = launch_arnoldi2d(a_, rq_, ctx_->stream) == hipSuccess;
+    if (!queued_) {
+        (void)hipGetLastError();
+        rq_ = 0;
+    }
+    return queued_;
 }
 
-int ArnoldiSteps::wait() {
-    if (rq) TGDK_HIP(hipMemcpyAsync(ctl_, a_.ctl, sizeof(ctl_), hipMemcpyDeviceToHost, ctx_->stream));
+int ArnoldiSteps::wait(bool* missed) {
+    if (queued_) TGDK_HIP(hipMemcpyAsync(ctl_, a_.ctl, sizeof(ctl_), hipMemcpyDeviceToHost, ctx_->stream));
     TGDK_HIP(hipStreamSynchronize(ctx_->stream));
-    return rq && ctl_[1] ? fail(TGDK_E_HIP, "the Arnoldi steps stopped making progress") : TGDK_OK;
+    *missed = queued_ && !ctl_[0];
+    if (*missed) rq_ = 0;
+    const bool dead = queued_ && ctl_[1];
+    queued_ = false;
+    return dead ? fail(TGDK_E_HIP, "the Arnoldi steps stopped making progress") : TGDK_OK;
 }
 
 void ArnoldiSteps::release() {
@@ -426,6 +434,12 @@ int tgdk_ctx_destroy(tgdk_ctx c) {
 }
 
 int tgdk_ctx_num_cus(tgdk_ctx c) { return c ? c->num_cus : 0; }
+
+int tgdk_ctx_one_launch(tgdk_ctx c, int mode) {
+    if (!c || mode < TGDK_ONE_LAUNCH_OFF || mode > TGDK_ONE_LAUNCH_CLOSED) return fail(TGDK_E_INVALID, "bad argument");
+    c->one_launch = mode;
+    return TGDK_OK;
+}
 
 static_assert(TGDK_STEP_NONE == ACT_NONE && TGDK_STEP_A == ACT_A && TGDK_STEP_A0 == ACT_A0 && TGDK_STEP_B == ACT_B && TGDK_STEP_RES == ACT_RES &&
                   TGDK_STEP_REDUCE == ACT_REDUCE && TGDK_STEP_APPLY == ACT_APPLY && TGDK_STEP_FIN == ACT_FIN &&

@@ -125,14 +125,10 @@ extern "C" int tgdk_coarse_setup(tgdk_op op, const double* b, double* x, const t
     // A M^{-1}; x accumulates u and becomes M^{-1} u at the end
     double* pz = prm->precond ? w + n : nullptr;
     int prc = TGDK_OK;
-    if (!pz && (rc = steps1.init(dop, m, H1, H2, Nd))) {
-        cleanup();
-        return rc;
-    }
+    if (!pz) steps1.init(dop, m, H1, H2, Nd);
     // steps j0 .. m - 1; after a restart column j0 is first re-orthogonalised
     // against the ones before it
-    auto arnoldi = [&](int j0) -> int {
-        if (steps1.rq) return steps1.run(j0, m, j0 > 0, V);
+    auto step_by_step = [&](int j0) {
         if (j0 > 0) {
             double* vk = V + (size_t)j0 * n;
             launch_gs_dot(V, n, j0, vk, n, H1, part, cnt, s);  // column 0 of H1/H2 is scratch here
@@ -152,15 +148,20 @@ extern "C" int tgdk_coarse_setup(tgdk_op op, const double* b, double* x, const t
             launch_gs_update_norm(V, n, j + 1, w, H2 + (size_t)j * (m + 1), n, Nd + j, part, cnt, s);
             launch_scale(w, V + (size_t)(j + 1) * n, Nd + j, n, s);
         }
-        return TGDK_OK;
+    };
+    auto arnoldi = [&](int j0) {
+        if (!steps1.run(j0, m, j0 > 0, V)) step_by_step(j0);
     };
     std::vector<double> h1(hsz), h2(hsz), nrm(m);
     auto fetch_columns = [&](std::vector<double>& Hbar, int j0) -> int {
-        TGDK_HIP(hipMemcpyAsync(h1.data(), H1, sizeof(double) * hsz, hipMemcpyDeviceToHost, s));
-        TGDK_HIP(hipMemcpyAsync(h2.data(), H2, sizeof(double) * hsz, hipMemcpyDeviceToHost, s));
-        TGDK_HIP(hipMemcpyAsync(nrm.data(), Nd, sizeof(double) * m, hipMemcpyDeviceToHost, s));
-        const int wrc = steps1.wait();
-        if (wrc) return wrc;
+        for (bool missed = true; missed;) {
+            TGDK_HIP(hipMemcpyAsync(h1.data(), H1, sizeof(double) * hsz, hipMemcpyDeviceToHost, s));
+            TGDK_HIP(hipMemcpyAsync(h2.data(), H2, sizeof(double) * hsz, hipMemcpyDeviceToHost, s));
+            TGDK_HIP(hipMemcpyAsync(nrm.data(), Nd, sizeof(double) * m, hipMemcpyDeviceToHost, s));
+            const int wrc = steps1.wait(&missed);
+            if (wrc) return wrc;
+            if (missed) step_by_step(j0);
+        }
         for (int j = j0; j < m; ++j) {
             for (int i = 0; i <= j; ++i)
                 Hbar[(size_t)i * m + j] = h1[(size_t)j * (m + 1) + i] + h2[(size_t)j * (m + 1) + i];
@@ -181,10 +182,7 @@ extern "C" int tgdk_coarse_setup(tgdk_op op, const double* b, double* x, const t
     }
     const double bnorm = beta;
     launch_scale(b, V, dsc, n, s);
-    if ((rc = arnoldi(0))) {
-        cleanup();
-        return rc;
-    }
+    arnoldi(0);
     std::vector<double> Hbar(hsz, 0.0), c(m + 1, 0.0), y(m), q(m + 1);
     if ((rc = fetch_columns(Hbar, 0))) {
         cleanup();
@@ -317,10 +315,7 @@ extern "C" int tgdk_coarse_setup(tgdk_op op, const double* b, double* x, const t
         }
         std::swap(V, Vt);
         // re-orthogonalise v_{k+1} against v_1..v_k, then continue Arnoldi
-        if ((rc = arnoldi(kk))) {
-            cleanup();
-            return rc;
-        }
+        arnoldi(kk);
         mvps += m - kk;
         Hbar = Hn;
         c = cn;

@@ -85,6 +85,7 @@ struct tgdk_ctx_s {
     tgdk::DevPool pool;
     tgdk::Mirror* mirror = nullptr;  // host-mapped
     int mirror_cap = 0;
+    int one_launch = TGDK_ONE_LAUNCH_ON;
     std::vector<hipEvent_t> events;
     // step-kernel timing for measurement: 0 off, 1 device-clock stamps,
     // 2 a HIP timing event after every step launch (tevents)
@@ -133,19 +134,28 @@ struct tgdk_defl_s {
 
 namespace tgdk {
 
+// First value of the one-launch kernels' gates.
+inline unsigned one_launch_gate(tgdk_ctx ctx) { return ctx->one_launch == TGDK_ONE_LAUNCH_CLOSED ? RES_GATE_CLOSED : 0; }
+
 // A cycle's Arnoldi steps in one launch (kernels_arnoldi2d.hip) for a basis of
 // up to m + 1 columns; H1, H2 with columns of m + 1, nrm: m values.
 struct ArnoldiSteps {
     explicit ArnoldiSteps(tgdk_ctx ctx) : ctx_(ctx) {}
-    int rq = 0;  // 0 (not initialised, or the one-launch form does not apply): the steps are launched one by one
-    int init(const DevOp& op, int m, double* H1, double* H2, double* nrm);
-    int run(int j0, int j1, bool reorth, double* V);  // enqueue, on basis V
-    int wait();  // for the stream, in either form; an error if the kernel gave up
+    void init(const DevOp& op, int m, double* H1, double* H2, double* nrm);
+    // Enqueues the steps on basis V; false where the caller has to launch them
+    // one by one (not initialised, the form does not apply, no memory for the
+    // exchange, or the launch was refused).
+    bool run(int j0, int j1, bool reorth, double* V);
+    // For the stream, in either form; an error if the kernel gave up.  *missed:
+    // the steps of run() did not begin (the chip was taken): launch them one by one.
+    int wait(bool* missed);
     void release();
 
 private:
     tgdk_ctx ctx_;
     ArnArgs a_;
+    int rq_ = 0;           // rows per wave of a tile; 0: one by one
+    bool queued_ = false;  // run() enqueued steps since the last wait()
     void* block_ = nullptr;
     unsigned ctl_[2] = {0, 0};
 };

@@ -146,7 +146,9 @@ __global__ __launch_bounds__(RT) void k_arnoldi2d(ArnArgs A) {
         ra.xstride = 0;
         ra.xch = A.xch;
         ra.ctl = A.ctl;
-        res_team(M, S, ra);
+        res_place(M, ra);
+        if (!res_enter<true>(M, S, ra)) return;
+        if (M.w == 0 && t == 0) A.ctl[0] = 1;  // begun
     }
     ResTile<RQ, VAR> tl;
     tl.set(M, A.op);
@@ -288,16 +290,16 @@ long long arnoldi2d_words(int team, int pmax) {
     return 3 * RES_NSUM * tp + 3 * RES_COPIES * RES_TOTALS + 3LL * team * RHALO + 2LL * pmax * (tp + 1);
 }
 
-__global__ __launch_bounds__(256) void k_arn_empty(u64* x, long long words, unsigned* ctl) {
+__global__ __launch_bounds__(256) void k_arn_empty(u64* x, long long words, unsigned* ctl, unsigned gate0) {
     for (long long i = blockIdx.x * 256LL + threadIdx.x; i < words; i += gridDim.x * 256LL) x[i] = RES_EMPTY;
-    if (blockIdx.x == 0 && threadIdx.x < 2) ctl[threadIdx.x] = 0;
+    if (blockIdx.x == 0 && threadIdx.x < 3) ctl[threadIdx.x] = threadIdx.x < 2 ? 0 : gate0;
 }
 
 hipError_t launch_arnoldi2d(const ArnArgs& args, int rq, hipStream_t s) {
     const long long words = arnoldi2d_words(args.team, args.pmax);
     const long long nb = (words + 1023) / 1024;
     hipLaunchKernelGGL(k_arn_empty, dim3((unsigned)(nb < 1024 ? nb : 1024)), dim3(256), 0, s, (u64*)args.xch, words,
-                       args.ctl);
+                       args.ctl, args.gate0);
     ArnArgs a = args;
     void* av[] = {&a};
     return hipLaunchCooperativeKernel(args.op.var ? arn_kernel<true>(rq) : arn_kernel<false>(rq), dim3(args.team),

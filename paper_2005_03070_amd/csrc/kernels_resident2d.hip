@@ -52,7 +52,8 @@ __global__ __launch_bounds__(RT) void k_resident2d(ResArgs A) {
     __shared__ BiLds<VAR, TI> S;
     const int t = threadIdx.x, lane = t & 63, wave = uniform(t >> 6);
     ResTeam M;
-    res_team(M, S, A);
+    res_place(M, A);
+    if (!res_enter<false>(M, S, A)) return;
     const TI none[RQ] = {};
     double dummy = 0.0;
     for (;;) {
@@ -233,12 +234,13 @@ __global__ __launch_bounds__(RT) void k_resident2d(ResArgs A) {
     }
 }
 
-// Empties the exchange regions, stores the descriptors that came as
+// Sets the queue, the abort word and the gates, empties the exchange regions, stores the descriptors that came as
 // arguments and writes every system's initial state.
-__global__ __launch_bounds__(256) void k_res_setup(ResArgs A, ResProbs Q, long long words) {
+__global__ __launch_bounds__(256) void k_res_setup(ResArgs A, ResProbs Q, long long words, int teams) {
     u64* x = (u64*)A.xch;
     for (long long i = blockIdx.x * 256LL + threadIdx.x; i < words; i += gridDim.x * 256LL) x[i] = RES_EMPTY;
-    if (blockIdx.x == 0 && threadIdx.x < 2) A.ctl[threadIdx.x] = 0;
+    if (blockIdx.x == 0)
+        for (int i = threadIdx.x; i < 2 + teams; i += 256) A.ctl[i] = i < 2 ? 0 : A.gate0;
     if (A.upload && blockIdx.x == 0) {
         const u64* src = reinterpret_cast<const u64*>(&Q);
         u64* dst = reinterpret_cast<u64*>(A.probs);
@@ -266,7 +268,7 @@ void launch_res_setup(const ResArgs& args, const DevProb* probs, int teams, hipS
     ResProbs q;
     memset(&q, 0, sizeof(q));
     for (int j = 0; args.upload && j < args.nprob; ++j) q.p[j] = probs[j];
-    hipLaunchKernelGGL(k_res_setup, dim3((unsigned)(nb < 1024 ? nb : 1024)), dim3(256), 0, s, args, q, words);
+    hipLaunchKernelGGL(k_res_setup, dim3((unsigned)(nb < 1024 ? nb : 1024)), dim3(256), 0, s, args, q, words, teams);
 }
 
 hipError_t launch_resident2d(int inner_f32, int var, const ResArgs& args, const DevProb* probs, int teams,

@@ -69,7 +69,7 @@ __global__ __launch_bounds__(RT) void k_resident_idr(ResArgs A, const double* P6
     __shared__ IdrLds<TI, SM, RQ> S;
     const int t = threadIdx.x, lane = t & 63, wave = uniform((int)(t >> 6));
     ResTeam M;
-    res_team(M, S, A);
+    res_place(M, A);
     const DevProb& P = A.probs[0];
     SolveState* st = P.st;
     const int k = uniform(P.k), maxit = A.init.maxit;
@@ -125,6 +125,7 @@ __global__ __launch_bounds__(RT) void k_resident_idr(ResArgs A, const double* P6
     }
     const TI none[RQ] = {};
     double dummy = 0.0;
+    if (!res_enter<false>(M, S, A)) return;
     bool any = false;
     int mvps = 0, inner = IN_CONVERGED;
     for (;;) {
@@ -353,7 +354,10 @@ __global__ __launch_bounds__(RT) void k_resident_idr(ResArgs A, const double* P6
             S.iters_total += mvps;
         }
     }
-    if (leader) res_end(S, st, mvps, inner);
+    if (leader) {
+        A.ctl[0] = 1;  // the solve ran
+        res_end(S, st, mvps, inner);
+    }
 }
 
 template <bool VAR, class TI, int SM>

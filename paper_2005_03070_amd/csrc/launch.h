@@ -65,8 +65,9 @@ hipError_t launch_resident_idr(int inner_f32, int var, const ResArgs& args, cons
 // multiplied by A, orthogonalised twice against columns 0 .. j (coefficients
 // to H1 and H2, column j at j ldh), its norm to nrm[j], normalised into column
 // j + 1.  reorth: column j0 itself is first orthogonalised against the ones
-// before it and normalised.  xch: arnoldi2d_words(team, pmax) words, ctl: two
-// words ([1] raised when a wait has timed out).
+// before it and normalised.  xch: arnoldi2d_words(team, pmax) words, ctl: three
+// words ([0] set when the steps began, [1] raised when a wait has timed out, [2]
+// the gate, gate0 its first value).
 struct ArnArgs {
     DevOp op;
     double* V;
@@ -74,6 +75,7 @@ struct ArnArgs {
     int ldh, j0, j1, reorth, team, pmax;
     void* xch;
     unsigned* ctl;
+    unsigned gate0;
 };
 // Rows per wave of a tile (0: the one-launch steps do not apply: 3-D, more than
 // 128 columns, or more tiles than max_team), and the workgroups they need.

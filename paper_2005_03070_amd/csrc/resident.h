@@ -20,10 +20,14 @@
 // second hop, each value gathered by one workgroup and its total read by all
 // (2.6 us with 256): 256 readers of 256 slots a value crowd the memory.
 //
-// Every workgroup of the grid must be resident: the kernels are launched
-// cooperatively with at most one workgroup per compute unit.  A poll that
-// outlasts RES_WAIT_TICKS raises the grid's abort word, which every poll
-// watches, so the kernel ends (the host then reports an error).
+// Every workgroup of a team must be resident: the kernels are launched
+// cooperatively with at most one workgroup per compute unit, and a team begins
+// at a gate that all its workgroups have to reach (res_gate): a kernel of
+// another stream or process may hold a unit for as long as it likes.  A team
+// that waits there for RES_GATE_TICKS ends without having touched anything, and
+// where no team began the host takes the kernels that need no residency.  Past
+// the gate a poll that outlasts RES_WAIT_TICKS raises the grid's abort word,
+// which every poll watches, so the kernel ends (the host reports an error).
 #pragma once
 
 #include "device_common.h"
@@ -42,6 +46,24 @@ __device__ __forceinline__ void res_store_bits(u64* p, u64 v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ void res_store(u64* p, double v) { res_store_bits(p, __builtin_bit_cast(u64, v)); }
+// Whether all `team` workgroups of a team reached the gate (thread 0 of each
+// calls it).  The word counts arrivals; one that has waited too long closes the
+// gate, which it can only while some are missing, so all get the same answer:
+// the word is `team` once and for all, or has RES_GATE_CLOSED set.  About 5 us
+// with 256 workgroups, once a launch.
+constexpr long long RES_GATE_TICKS = 100000000;  // 1 s
+__device__ __forceinline__ bool res_gate(unsigned* word, unsigned team) {
+    unsigned v = __hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
+    const long long t0 = wall_clock64();
+    while (v < team) {
+        v = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (v < team && wall_clock64() - t0 > RES_GATE_TICKS &&
+            __hip_atomic_compare_exchange_strong(word, &v, v | RES_GATE_CLOSED, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT))
+            return false;
+    }
+    return v == team;
+}
 // A caller's vector may hold any bit pattern: the empty one becomes another NaN.
 __device__ __forceinline__ double res_quiet(double v) {
     const u64 b = __builtin_bit_cast(u64, v);

@@ -540,7 +540,7 @@ __device__ __forceinline__ int res_boundary(ResTeam& M, ResLds& S, const ResArgs
 }
 
 // This workgroup's team and place in it.
-__device__ __forceinline__ void res_team(ResTeam& M, ResLds& S, const ResArgs& A) {
+__device__ __forceinline__ void res_place(ResTeam& M, const ResArgs& A) {
     const int team = blockIdx.x / A.team;
     M.T = A.team;
     M.w = blockIdx.x - team * A.team;
@@ -549,8 +549,28 @@ __device__ __forceinline__ void res_team(ResTeam& M, ResLds& S, const ResArgs& A
     M.abort_word = A.ctl + 1;
 #pragma unroll
     for (int i = 0; i < 4; ++i) M.nbr[i] = -1;
-    if (threadIdx.x == 0) S.dead = 0;
+}
+
+static __device__ __attribute__((noinline)) bool res_gate_call(unsigned* word, unsigned team) {
+    return res_gate(word, team);
+}
+
+// Whether the team begins (its gate is word 2 + team of A.ctl).  Where a kernel
+// enters and whether the gate is a CALL is a matter of registers: past the gate's
+// atomics the compiler no longer takes what it reads for unchanged.  The IDR kernels
+// enter after they have read their descriptor (first, the 64-row ones of coefficient
+// arrays spill 186 registers instead of 144), the others first; the Arnoldi kernels
+// through a call (64 rows, inlined: 60 instead of 42, 2 % of a cycle at 1023^2),
+// BiCGStab's without (with it 1 % of a solve with coefficient arrays).
+template <bool CALL>
+__device__ __forceinline__ bool res_enter(const ResTeam& M, ResLds& S, const ResArgs& A) {
+    if (threadIdx.x == 0) {
+        unsigned* word = A.ctl + 2 + blockIdx.x / A.team;
+        S.dead = 0;
+        S.stop = !(CALL ? res_gate_call(word, (unsigned)M.T) : res_gate(word, (unsigned)M.T));
+    }
     __syncthreads();
+    return uniform(S.stop) == 0;
 }
 
 }  // namespace tgdk

@@ -207,7 +207,7 @@ static int tile_count(const tgdk_op op, int rows) {
 }
 
 static int resident_team(tgdk_ctx ctx, const std::vector<ProbSpec>& ps, const tgdk_solve_params* prm, int idr_s) {
-    if (ps[0].op->dim != 2) return 0;
+    if (ps[0].op->dim != 2 || ctx->one_launch == TGDK_ONE_LAUNCH_OFF) return 0;
     int rows = RES_TILE;
     if (prm->method == TGDK_IDRS_PROJ) {
         rows = prm->precond ? 0 : resident_idr_rows(idr_s, make_devop(ps[0].op, 0), std::min(ctx->num_cus, 256));
@@ -232,9 +232,10 @@ static void set_space(DevProb& P, tgdk_defl d) {
 }
 
 // Fills the device-side group description and workspaces (allocated in the
-// context's grow-only buffer, or laid out in ext).
+// context's grow-only buffer, or laid out in ext).  one: as a one-launch solve
+// where that applies.
 static int build_group(tgdk_ctx ctx, const std::vector<ProbSpec>& ps, const tgdk_solve_params* prm, Group& g,
-                       const ExtWs* ext = nullptr, int idr_s = 0) {
+                       const ExtWs* ext = nullptr, int idr_s = 0, bool one = true) {
     g.ctx = ctx;
     g.nprob = (int)ps.size();
     g.dim = ps[0].op->dim;
@@ -269,7 +270,7 @@ static int build_group(tgdk_ctx ctx, const std::vector<ProbSpec>& ps, const tgdk
     // phases at n_x = 255); x, b and V keep the caller's pitch n_x.  The
     // other drivers' kernels and the 2-D tile paths assume pitch n_x.
     const bool padded = g.dim == 3 && prm->method == TGDK_BICGSTAB_PROJ;
-    g.team = resident_team(ctx, ps, prm, idr_s);
+    g.team = one ? resident_team(ctx, ps, prm, idr_s) : 0;
     std::vector<size_t> nstore(g.nprob);  // elements per stored vector
     for (int j = 0; j < g.nprob; ++j) {
         const tgdk_op op = ps[j].op;
@@ -326,14 +327,16 @@ static int build_group(tgdk_ctx ctx, const std::vector<ProbSpec>& ps, const tgdk
     if (stamps) off += align256(sizeof(unsigned long long) * 2 * NTSLOG * (size_t)g.probs[0].nwg);
     int rc;
     char* base;
-    // the resident solve's workspace: descriptors, states, exchange regions
+    // the resident solve's workspace: descriptors, states, control words (one
+    // copy to the host takes both), exchange regions
+    const size_t off_ctl = off_states + sizeof(SolveState) * g.nprob;
     size_t res_xch = 0;
     if (g.team) {
         g.teams = std::max(1, std::min(g.nprob, std::min(ctx->num_cus, 256) / g.team));
         g.res.kmax = 0;
         for (const DevProb& P : g.probs) g.res.kmax = std::max(g.res.kmax, P.k);
         g.res.xstride = res_exchange_words(g.team, g.res.kmax);
-        res_xch = align256(off_counters + 256);
+        res_xch = align256(off_ctl + sizeof(unsigned) * (2 + (size_t)g.teams));
         const size_t need = res_xch + align256((size_t)g.res.xstride * g.teams * 8);
         // (in a caller's workspace both have to fit, so that the step
         // kernel's decides what is refused; a few KB of vectors can be less
@@ -368,7 +371,8 @@ static int build_group(tgdk_ctx ctx, const std::vector<ProbSpec>& ps, const tgdk
         a.probs = g.d_probs;
         a.nprob = g.nprob;
         a.team = g.team;
-        a.ctl = counters;
+        a.ctl = (unsigned*)(base + off_ctl);
+        a.gate0 = one_launch_gate(ctx);
         a.xch = base + res_xch;
         a.states = g.d_states;
         a.upload = g.nprob <= RES_ARGPROBS;
@@ -395,7 +399,7 @@ static int build_group(tgdk_ctx ctx, const std::vector<ProbSpec>& ps, const tgdk
         if (!a.upload)
             TGDK_HIP(hipMemcpyAsync(g.d_probs, g.probs.data(), sizeof(DevProb) * g.nprob, hipMemcpyHostToDevice,
                                     ctx->stream));
-        g.states.assign(g.nprob, SolveState());
+        g.states.assign(g.nprob + 1, SolveState());  // and the control words
         return TGDK_OK;
     }
     g.states.assign(g.nprob, SolveState());
@@ -531,6 +535,8 @@ static long long count_vops(const SolveState& S, int k, int idr_s, const std::ve
     return v;
 }
 
+constexpr int NOT_BEGUN = 1000;  // a one-launch solve that did not begin
+
 // cycle_steps: the GMRES driver's steps per cycle (one right-hand side);
 // the other solvers' per-cycle counts come from the device's cycle log.
 // idr_s: the shadow-space dimension of an IDR(s) solve (0 otherwise).
@@ -540,8 +546,15 @@ static int finish_group(Group& g, const std::vector<ProbSpec>& ps, tgdk_solve_re
     hipStream_t s = g.ctx->stream;
     if (!g.team) launch(g, K_RESIDUAL, 2);  // (the resident solve ends with the true residual)
     TGDK_HIP(hipGetLastError());
-    TGDK_HIP(hipMemcpyAsync(g.states.data(), g.d_states, sizeof(SolveState) * g.nprob, hipMemcpyDeviceToHost, s));
+    unsigned ctl[2];
+    TGDK_HIP(hipMemcpyAsync(g.states.data(), g.d_states, sizeof(SolveState) * g.nprob + (g.team ? sizeof(ctl) : 0),
+                            hipMemcpyDeviceToHost, s));
     TGDK_HIP(hipStreamSynchronize(s));
+    if (g.team) {
+        memcpy(ctl, &g.states[g.nprob], sizeof(ctl));
+        if (ctl[1]) return fail(TGDK_E_HIP, "the resident solve stopped making progress");
+        if (!ctl[0]) return NOT_BEGUN;
+    }
     int rc = TGDK_OK;
     for (int j = 0; j < g.nprob; ++j) {
         const SolveState& S = g.states[j];
@@ -617,24 +630,27 @@ static int predict_steps(const Mirror& m, Predict& pr) {
 
 // The chip-resident solve: one launch runs every system of the group to its
 // end; the host waits for it.  idr_s > 0: IDR(s) with the shadow columns P64.
+// NOT_BEGUN: the launch was refused, or the chip was taken; nothing has changed.
 static int resident_group(Group& g, const std::vector<ProbSpec>& ps, tgdk_solve_report* reps,
                           std::chrono::steady_clock::time_point t0, int idr_s = 0, const double* P64 = nullptr,
                           double kappa = 0.0) {
     tgdk_ctx ctx = g.ctx;
     hipStream_t s = ctx->stream;
+    hipError_t e;
     if (idr_s > 0)
-        TGDK_HIP(launch_resident_idr(g.inner_f32, g.var, g.res, g.probs.data(), P64, idr_s,
-                                     resident_idr_rows(idr_s, g.probs[0].op, std::min(ctx->num_cus, 256)), kappa, s));
+        e = launch_resident_idr(g.inner_f32, g.var, g.res, g.probs.data(), P64, idr_s,
+                                resident_idr_rows(idr_s, g.probs[0].op, std::min(ctx->num_cus, 256)), kappa, s);
     else
-        TGDK_HIP(launch_resident2d(g.inner_f32, g.var, g.res, g.probs.data(), g.teams, s));
+        e = launch_resident2d(g.inner_f32, g.var, g.res, g.probs.data(), g.teams, s);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        return NOT_BEGUN;
+    }
     TGDK_HIP(hipEventRecord(ctx->events[0], s));
-    int rc = wait_event(ctx->events[0]);
+    const int rc = wait_event(ctx->events[0]);
     if (rc) return rc;
     const double secs = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
-    unsigned ctl[2] = {0, 0};
-    TGDK_HIP(hipMemcpyAsync(ctl, g.res.ctl, sizeof(ctl), hipMemcpyDeviceToHost, s));
-    rc = finish_group(g, ps, reps, secs, nullptr, nullptr, idr_s);
-    return ctl[1] ? fail(TGDK_E_HIP, "the resident solve stopped making progress") : rc;
+    return finish_group(g, ps, reps, secs, nullptr, nullptr, idr_s);
 }
 
 // BiCGStab(ncyc)-Proj(k) over a group: step launches only.  At most two
@@ -649,7 +665,11 @@ static int bicgstab_group(tgdk_ctx ctx, const std::vector<ProbSpec>& ps, const t
     int rc = build_group(ctx, ps, prm, g, ext);
     if (rc) return rc;
     if (!ext && (rc = ensure_events(ctx, 2))) return rc;
-    if (g.team) return resident_group(g, ps, reps, t0);
+    if (g.team) {
+        if ((rc = resident_group(g, ps, reps, t0)) != NOT_BEGUN) return rc;
+        g = Group();
+        if ((rc = build_group(ctx, ps, prm, g, ext, 0, false))) return rc;
+    }
     hipStream_t s = ctx->stream;
     const int S_MAX = 24;  // largest batch of steps enqueued at once
     const long long max_cycles = prm->ncyc + (prm->max_extra_cycles >= 0 ? prm->max_extra_cycles : prm->ncyc) + 2;
@@ -835,7 +855,7 @@ static int gmres_single(tgdk_ctx ctx, const ProbSpec& p, const tgdk_solve_params
     std::vector<int> cyc_steps;  // steps of each cycle
     const DevOp op = make_devop(p.op, prm->transpose);
     ArnoldiSteps steps1(ctx);  // a cycle's steps in one launch, where that applies
-    if (!rc && !pre) rc = steps1.init(op, m, H1, H2, Nd);
+    if (!rc && !pre) steps1.init(op, m, H1, H2, Nd);
     const int maxcyc = prm->max_extra_cycles > 0 ? prm->max_extra_cycles : 1000;
     std::vector<double> h1(hsz), h2(hsz), nrm(m), Hbar(hsz), rhs(m + 1), y(m), res(m + 1);
     SolveState S;
@@ -856,28 +876,31 @@ static int gmres_single(tgdk_ctx ctx, const ProbSpec& p, const tgdk_solve_params
         // this cycle's length (variable restarting), at most m
         const int mc = cyc < prm->n_cycle_lengths && prm->cycle_lengths ? prm->cycle_lengths[cyc] : m;
         int steps = mc;
-        if (steps1.rq && (rc = steps1.run(0, mc, false, V))) break;
-        for (int j = 0; j < mc && !steps1.rq; ++j) {
-            if (pre) {  // right preconditioning: w = A M^{-1} v_j
-                if ((rc = prm->precond(prm->precond_user, V + (size_t)j * n, pz, 1))) break;
-                launch_apply<double>(op, pz, w, 1, p.op->tile_id[0], s);
-            } else {
-                launch_apply<double>(op, V + (size_t)j * n, w, 1, p.op->tile_id[0], s);
+        bool one = steps1.run(0, mc, false, V);
+        for (bool missed = true; missed && !rc; one = false) {
+            for (int j = 0; j < mc && !one; ++j) {
+                if (pre) {  // right preconditioning: w = A M^{-1} v_j
+                    if ((rc = prm->precond(prm->precond_user, V + (size_t)j * n, pz, 1))) break;
+                    launch_apply<double>(op, pz, w, 1, p.op->tile_id[0], s);
+                } else {
+                    launch_apply<double>(op, V + (size_t)j * n, w, 1, p.op->tile_id[0], s);
+                }
+                launch_gs_dot(V, n, j + 1, w, n, H1 + (size_t)j * (m + 1), (double*)ctx->partial.p, ctx->counters, s);
+                launch_gs_update_dot(V, n, j + 1, w, H1 + (size_t)j * (m + 1), n, H2 + (size_t)j * (m + 1),
+                                     (double*)ctx->partial.p, ctx->counters, s);
+                launch_gs_update_norm(V, n, j + 1, w, H2 + (size_t)j * (m + 1), n, Nd + j, (double*)ctx->partial.p,
+                                      ctx->counters, s);
+                launch_scale(w, V + (size_t)(j + 1) * n, Nd + j, n, s);
             }
-            launch_gs_dot(V, n, j + 1, w, n, H1 + (size_t)j * (m + 1), (double*)ctx->partial.p, ctx->counters, s);
-            launch_gs_update_dot(V, n, j + 1, w, H1 + (size_t)j * (m + 1), n, H2 + (size_t)j * (m + 1),
-                                 (double*)ctx->partial.p, ctx->counters, s);
-            launch_gs_update_norm(V, n, j + 1, w, H2 + (size_t)j * (m + 1), n, Nd + j, (double*)ctx->partial.p,
-                                  ctx->counters, s);
-            launch_scale(w, V + (size_t)(j + 1) * n, Nd + j, n, s);
+            if (rc) break;
+            TGDK_HIP(hipGetLastError());
+            TGDK_HIP(hipMemcpyAsync(h1.data(), H1, sizeof(double) * hsz, hipMemcpyDeviceToHost, s));
+            TGDK_HIP(hipMemcpyAsync(h2.data(), H2, sizeof(double) * hsz, hipMemcpyDeviceToHost, s));
+            TGDK_HIP(hipMemcpyAsync(nrm.data(), Nd, sizeof(double) * m, hipMemcpyDeviceToHost, s));
+            TGDK_HIP(hipMemcpyAsync(&S, g.d_states, sizeof(SolveState), hipMemcpyDeviceToHost, s));
+            rc = steps1.wait(&missed);
         }
         if (rc) break;
-        TGDK_HIP(hipGetLastError());
-        TGDK_HIP(hipMemcpyAsync(h1.data(), H1, sizeof(double) * hsz, hipMemcpyDeviceToHost, s));
-        TGDK_HIP(hipMemcpyAsync(h2.data(), H2, sizeof(double) * hsz, hipMemcpyDeviceToHost, s));
-        TGDK_HIP(hipMemcpyAsync(nrm.data(), Nd, sizeof(double) * m, hipMemcpyDeviceToHost, s));
-        TGDK_HIP(hipMemcpyAsync(&S, g.d_states, sizeof(SolveState), hipMemcpyDeviceToHost, s));
-        if ((rc = steps1.wait())) break;
         // Hbar (row-major (m+1) x m); stop at an exact zero subdiagonal
         std::fill(Hbar.begin(), Hbar.end(), 0.0);
         for (int j = 0; j < mc; ++j) {
@@ -955,7 +978,11 @@ static int idr_single(tgdk_ctx ctx, const ProbSpec& p, int s, const double* shad
     } while (0)
     IDR_HIP(hipMemcpyAsync(P64, shadow, sn * 8, hipMemcpyDeviceToDevice, hs));
     if ((rc = cholqr2(ctx, P64, n, s))) return done(rc == TGDK_E_SINGULAR ? fail(rc, "shadow space is rank deficient") : rc);
-    if (g.team) return done(resident_group(g, ps, rep, t0, s, P64, kappa));
+    if (g.team) {
+        if ((rc = resident_group(g, ps, rep, t0, s, P64, kappa)) != NOT_BEGUN) return done(rc);
+        g = Group();
+        if ((rc = build_group(ctx, ps, prm, g, nullptr, s, false))) return done(rc);
+    }
     if (f32) launch_to_f32(P64, (float*)(wk + off_p), (long long)sn, hs);
     IdrState h;
     memset(&h, 0, sizeof(h));

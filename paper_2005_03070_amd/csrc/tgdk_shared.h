@@ -160,6 +160,7 @@ constexpr int RES_TILE = 64;
 constexpr int RES_NSUM = 9;   // most sums of one exchange
 constexpr int RES_TOTALS = 16;  // words of a copy of their totals
 constexpr int RES_COPIES = 16;  // copies of an exchange's totals (read by different workgroups)
+constexpr unsigned RES_GATE_CLOSED = 0x10000;  // above every count of a team's workgroups
 constexpr int RES_ARGPROBS = 4;  // descriptors passed in the set-up kernel's arguments
 // A solve's parameters, the same for every system (names as in SolveState).
 struct ResInit {
@@ -173,7 +174,9 @@ struct ResArgs {
     int upload;              // the set-up kernel stores the descriptors of its arguments
     long long xstride;       // 64-bit words of a team's exchange region
     void* xch;               // the teams' exchange regions
-    unsigned* ctl;           // [0] next system, [1] raised when a wait has timed out
+    unsigned* ctl;           // [0] next system (0: no team began), [1] raised when a wait has timed
+                             // out, [2 + team] the teams' gates
+    unsigned gate0;          // the gates' first value (a closed one: no team is to begin)
     SolveState* states;
     ResInit init;
 };
