@@ -273,10 +273,19 @@ static const void* arn_kernel(int rq) {
     }
 }
 
+// The smallest tiles that fit the chip.  64-row tiles only where three quarters of
+// their columns are in the grid: a tile's pass takes as long with one column as
+// with 64, a pass over V as launches takes the points' time.  us a step as launches
+// and in one launch, 40 | 100 columns: 1 x 16384 38 and 69 | 55 and 136, 16 x 16384
+// 61 and 71 | 96 and 144, 48 x 16384 107 and 82 | 238 and 211, 130 x 4000 84 and
+// 78 | 160 and 184, 200 x 4000 107 and 90 | 233 and 215; 32-row tiles gain at any
+// width (1 x 4000 36 and 29 | 54 and 49, 65 x 4000 57 and 48 | 94 and 95).
 int arnoldi2d_rows(const DevOp& op, int pmax, int max_team, int* team) {
     if (op.dim != 2 || pmax > ARN_PMAX) return 0;
     for (int rq = 1; rq <= 8; rq *= 2) {
-        const long long tiles = (long long)((op.nx + RTILE - 1) / RTILE) * ((op.ny + RW * rq - 1) / (RW * rq));
+        const int tx = (op.nx + RTILE - 1) / RTILE;
+        const long long tiles = (long long)tx * ((op.ny + RW * rq - 1) / (RW * rq));
+        if (rq == 8 && 4LL * op.nx < 3LL * RTILE * tx) return 0;
         if (tiles <= max_team) {
             *team = (int)tiles;
             return rq;

@@ -78,7 +78,7 @@ struct ArnArgs {
     unsigned gate0;
 };
 // Rows per wave of a tile (0: the one-launch steps do not apply: 3-D, more than
-// 128 columns, or more tiles than max_team), and the workgroups they need.
+// 128 columns, more tiles than max_team, or mostly empty ones), and the workgroups they need.
 int arnoldi2d_rows(const DevOp& op, int pmax, int max_team, int* team);
 long long arnoldi2d_words(int team, int pmax);
 hipError_t launch_arnoldi2d(const ArnArgs& args, int rq, hipStream_t s);

@@ -149,6 +149,20 @@ def test_gmres(dims, m):
     assert np.linalg.norm(x.cpu().numpy() - xo) <= 1e-10 * np.linalg.norm(xo)  # as with one launch a cycle
 
 
+# tiles of 64 rows with 47 and 48 of their 64 columns in the grid: launches per
+# step, and one launch a cycle
+@pytest.mark.parametrize("nx", [47, 48])
+def test_gmres_on_narrow_grids(nx):
+    dims = (nx, 8300)
+    oop, op = O.const_cd(dims, (5.0, 2.0)), tg().Operator.const_cd(dims, (5.0, 2.0), device=DEV)
+    b = W.rhs(op.n, 12)
+    x, _ = tg().solve(op, _t(b), method="gmres", m3=12, rtol=1e-13, max_extra=2)
+    xo, _ = OG.gmres_proj(oop, b, rtol=1e-13, m=12, maxcyc=2)
+    assert np.linalg.norm(x.cpu().numpy() - xo) <= 1e-10 * np.linalg.norm(xo)
+    off, = _off_and_closed(lambda: [tg().solve(op, _t(b), method="gmres", m3=12, rtol=1e-13, max_extra=2)[0]])
+    assert torch.equal(x, off) == (nx == 47)  # (the sums of the one-launch steps have another order)
+
+
 def test_coarse_setup():
     dims = (63, 66)
     oop, op = O.const_cd(dims, (4.0, 1.0)), tg().Operator.const_cd(dims, (4.0, 1.0), device=DEV)
