@@ -27,7 +27,7 @@ int fail(int code, const std::string& msg) {
 int DevBuf::ensure(size_t bytes) {
     if (bytes <= cap) return TGDK_OK;
     release();
-    hipError_t e = hipMalloc(&p, bytes);
+    const hipError_t e = dev_malloc(device, &p, bytes);
     if (e != hipSuccess) {
         p = nullptr;
         cap = 0;
@@ -92,69 +92,6 @@ void ArnoldiSteps::release() {
     block_ = nullptr;
 }
 
-void DevPool::trim(size_t room) {
-    for (size_t i = 0; i < idle.size();) {  // oldest first
-        if (now - idle[i].stamp <= POOL_AGE && held + room <= POOL_BYTES) {
-            ++i;
-            continue;
-        }
-        held -= idle[i].bytes;
-        (void)hipFree(idle[i].p);
-        idle.erase(idle.begin() + i);
-    }
-}
-
-void* DevPool::get(size_t bytes) {
-    std::lock_guard<std::mutex> lock(mutex);
-    ++now;
-    size_t best = idle.size();
-    for (size_t i = 0; i < idle.size(); ++i)
-        if (idle[i].bytes >= bytes && idle[i].bytes - bytes <= idle[i].bytes / 8 &&
-            (best == idle.size() || idle[i].bytes < idle[best].bytes))
-            best = i;
-    void* p = nullptr;
-    if (best < idle.size()) {
-        p = idle[best].p;
-        taken[p] = idle[best].bytes;
-        held -= idle[best].bytes;
-        idle.erase(idle.begin() + best);
-        trim(0);
-        return p;
-    }
-    trim(0);
-    if (hipMalloc(&p, bytes) != hipSuccess) {
-        (void)hipGetLastError();
-        for (const Block& b : idle) (void)hipFree(b.p);
-        idle.clear();
-        held = 0;
-        if (hipMalloc(&p, bytes) != hipSuccess) return nullptr;
-    }
-    taken[p] = bytes;
-    return p;
-}
-
-void DevPool::put(void* p) {
-    if (!p) return;
-    std::lock_guard<std::mutex> lock(mutex);
-    const auto it = taken.find(p);
-    const size_t bytes = it == taken.end() ? POOL_BYTES + 1 : it->second;
-    if (it != taken.end()) taken.erase(it);
-    if (bytes > POOL_BYTES) {
-        (void)hipFree(p);
-        return;
-    }
-    trim(bytes);
-    idle.push_back({p, bytes, now});
-    held += bytes;
-}
-
-void DevPool::flush() {
-    std::lock_guard<std::mutex> lock(mutex);
-    for (const Block& b : idle) (void)hipFree(b.p);
-    idle.clear();
-    held = 0;
-}
-
 DevOp make_devop(const tgdk_op_s* op, int transpose) {
     DevOp d;
     memset(&d, 0, sizeof(d));
@@ -173,12 +110,9 @@ DevOp make_devop(const tgdk_op_s* op, int transpose) {
 }
 
 template <class T>
-static int dev_alloc(T** p, size_t count) {
-    hipError_t e = hipMalloc((void**)p, std::max<size_t>(count, 1) * sizeof(T));
-    if (e != hipSuccess) {
-        *p = nullptr;
-        return fail(TGDK_E_NOMEM, std::string("hipMalloc failed: ") + hipGetErrorString(e));
-    }
+static int dev_alloc(tgdk_ctx ctx, T** p, size_t count) {
+    const hipError_t e = dev_malloc(ctx->device, (void**)p, std::max<size_t>(count, 1) * sizeof(T));
+    if (e != hipSuccess) return fail(TGDK_E_NOMEM, std::string("hipMalloc failed: ") + hipGetErrorString(e));
     return TGDK_OK;
 }
 
@@ -387,14 +321,13 @@ int tgdk_ctx_create(tgdk_ctx* out, int device, void* hip_stream) {
     TGDK_HIP(hipSetDevice(device));
     hipDeviceProp_t prop;
     TGDK_HIP(hipGetDeviceProperties(&prop, device));
-    tgdk_ctx c = new tgdk_ctx_s();
-    c->device = device;
+    tgdk_ctx c = new tgdk_ctx_s(device);
     c->stream = (hipStream_t)hip_stream;
     c->num_cus = prop.multiProcessorCount;
-    if (hipMalloc((void**)&c->counters, 64 * sizeof(unsigned)) != hipSuccess ||
+    if (dev_malloc(device, (void**)&c->counters, 64 * sizeof(unsigned)) != hipSuccess ||
         hipMemset(c->counters, 0, 64 * sizeof(unsigned)) != hipSuccess ||
-        hipMalloc((void**)&c->dscal, 4096 * sizeof(double)) != hipSuccess ||
-        hipMalloc((void**)&c->zero, 4096) != hipSuccess || hipMemset(c->zero, 0, 4096) != hipSuccess ||
+        dev_malloc(device, (void**)&c->dscal, 4096 * sizeof(double)) != hipSuccess ||
+        dev_malloc(device, (void**)&c->zero, 4096) != hipSuccess || hipMemset(c->zero, 0, 4096) != hipSuccess ||
         hipHostMalloc((void**)&c->mirror, sizeof(Mirror) * MIRROR_PREALLOC, hipHostMallocMapped) != hipSuccess) {
         (void)tgdk_ctx_destroy(c);
         return fail(TGDK_E_NOMEM, "context allocation failed");
@@ -523,8 +456,8 @@ int tgdk_op_create(tgdk_ctx ctx, const tgdk_op_desc* d, tgdk_op* out) {
     hipStream_t s = ctx->stream;
     const long long N = op->N;
     int rc;
-    if ((rc = dev_alloc(&op->coef64, (size_t)nc * N)) || (rc = dev_alloc(&op->coefT64, (size_t)nc * N)) ||
-        (rc = dev_alloc(&op->coef32, (size_t)nc * N)) || (rc = dev_alloc(&op->coefT32, (size_t)nc * N))) {
+    if ((rc = dev_alloc(ctx, &op->coef64, (size_t)nc * N)) || (rc = dev_alloc(ctx, &op->coefT64, (size_t)nc * N)) ||
+        (rc = dev_alloc(ctx, &op->coef32, (size_t)nc * N)) || (rc = dev_alloc(ctx, &op->coefT32, (size_t)nc * N))) {
         tgdk_op_destroy(op);
         return rc;
     }
@@ -536,7 +469,7 @@ int tgdk_op_create(tgdk_ctx ctx, const tgdk_op_desc* d, tgdk_op* out) {
         }
     } else {
         const size_t ncell = (size_t)(op->n[0] + 1) * (op->n[1] + 1);
-        if ((rc = dev_alloc(&op->kcell, ncell))) {
+        if ((rc = dev_alloc(ctx, &op->kcell, ncell))) {
             tgdk_op_destroy(op);
             return rc;
         }
@@ -573,7 +506,7 @@ int tgdk_op_coarsen(tgdk_op fine, tgdk_op* coarse) {
     if (fine->kind == TGDK_CONST_CD) return tgdk_op_create(fine->ctx, &d, coarse);
     double* kc = nullptr;
     const size_t ncell = (size_t)(d.n[0] + 1) * (d.n[1] + 1);
-    int rc = dev_alloc(&kc, ncell);
+    int rc = dev_alloc(fine->ctx, &kc, ncell);
     if (rc) return rc;
     launch_coarsen_kcell(d.n[0], d.n[1], fine->kcell, kc, fine->ctx->stream);
     d.coef = kc;
@@ -837,8 +770,8 @@ int tgdk_tune(tgdk_ctx ctx, tgdk_op op, int dtype, int nrhs, int* tile_y) {
     const size_t bytes = (size_t)op->N * nrhs * es;
     void* x = nullptr;
     void* y = nullptr;
-    TGDK_HIP(hipMalloc(&x, bytes));
-    if (hipMalloc(&y, bytes) != hipSuccess) {
+    TGDK_HIP(dev_malloc(op->ctx->device, &x, bytes));
+    if (dev_malloc(op->ctx->device, &y, bytes) != hipSuccess) {
         (void)hipFree(x);
         return fail(TGDK_E_NOMEM, "tune buffers");
     }

@@ -3,13 +3,12 @@
 
 #include <hip/hip_runtime.h>
 
-#include <mutex>
 #include <string>
-#include <unordered_map>
 #include <vector>
 
 #include "../../include/tgdk.h"
 #include "launch.h"
+#include "pool.h"
 #include "tgdk_shared.h"
 
 namespace tgdk {
@@ -26,6 +25,8 @@ int fail(int code, const std::string& msg);
 
 // Device buffer that grows on demand (contents not preserved on growth).
 struct DevBuf {
+    explicit DevBuf(int dev) : device(dev) {}
+    const int device;
     void* p = nullptr;
     size_t cap = 0;
     int ensure(size_t bytes);
@@ -33,50 +34,15 @@ struct DevBuf {
     ~DevBuf() { release(); }
 };
 
-// Device memory of deflation spaces and of the calls that build and use them,
-// kept for the next call.  Handing large blocks back to the driver and taking
-// them again costs little in one call, but the driver clears what it is handed
-// back, and a program that moves one space after another waits for that: moving
-// 30 vectors to 1023^2 takes 2.8 ms the first times and 21 ms from then on
-// (2.3 GB a call handed back and cleared).
-//
-// A block is reused for requests of its size or up to an eighth less.  At most
-// POOL_BYTES are held free, and a block that no one took for POOL_AGE requests
-// goes back to the driver.  The pool belongs to a context, hence to one stream:
-// whatever still uses a block's old contents is ordered before its next use.
-// Handles may be destroyed from any thread (a garbage collector's), so the
-// pool has a lock.
-constexpr size_t POOL_BYTES = (size_t)2 << 30;
-constexpr unsigned POOL_AGE = 64;
-class DevPool {
-public:
-    void* get(size_t bytes);  // null: no memory
-    void put(void* p);
-    void flush();
-    ~DevPool() { flush(); }
-
-private:
-    struct Block {
-        void* p;
-        size_t bytes;
-        unsigned long long stamp;
-    };
-    void trim(size_t room);  // hands back old blocks, and the oldest until `room` more bytes fit
-    std::mutex mutex;
-    std::vector<Block> idle;
-    std::unordered_map<void*, size_t> taken;
-    size_t held = 0;
-    unsigned long long now = 0;
-};
-
 }  // namespace tgdk
 
 struct tgdk_ctx_s {
-    int device = 0;
+    explicit tgdk_ctx_s(int dev) : device(dev), partial(dev), solve_ws(dev), pool(dev) {}
+    const int device;
     hipStream_t stream = nullptr;
     int num_cus = 0;
     // scratch for the dense and Gram-Schmidt kernels
-    tgdk::DevBuf partial;      // doubles
+    tgdk::DevBuf partial;  // doubles
     unsigned* counters = nullptr;  // 64 zero-initialised counters
     double* dscal = nullptr;   // small device scalar area (4096 doubles)
     void* zero = nullptr;      // 4 KiB of zeros, never written

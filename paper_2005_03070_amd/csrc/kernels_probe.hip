@@ -204,7 +204,7 @@ extern "C" int tgdk_stream_probe(tgdk_ctx ctx, int pattern, int nreads, int nwri
     };
     TGDK_HIP(hipSetDevice(ctx->device));
     for (int i = 0; i < ns; ++i) {
-        if (hipMalloc((void**)&bufs[i], (size_t)n * 8) != hipSuccess) {
+        if (dev_malloc(ctx->device, (void**)&bufs[i], (size_t)n * 8) != hipSuccess) {
             release();
             return fail(TGDK_E_NOMEM, "probe buffers");
         }

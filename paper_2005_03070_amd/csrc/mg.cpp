@@ -173,7 +173,7 @@ int tgdk_mg_create(tgdk_op op, int cycles, int nu, int flags, tgdk_mg* out) {
     for (size_t l = 0; l < mg->ops.size() && !rc; ++l) {
         const size_t n = (size_t)mg->ops[l]->N;
         double* p = nullptr;
-        if (hipMalloc((void**)&p, sizeof(double) * n * (l == 0 ? 5 : 3)) != hipSuccess) {
+        if (dev_malloc(op->ctx->device, (void**)&p, sizeof(double) * n * (l == 0 ? 5 : 3)) != hipSuccess) {
             rc = fail(TGDK_E_NOMEM, "multigrid level allocation failed");
             break;
         }
@@ -203,7 +203,7 @@ int tgdk_mg_create(tgdk_op op, int cycles, int nu, int flags, tgdk_mg* out) {
         MgTail P;
         mg->tail = plan_tail(mg, P);
         if (mg->tail < (int)mg->ops.size()) {
-            if (hipMalloc((void**)&mg->tail_dev, sizeof(MgTail)) != hipSuccess)
+            if (dev_malloc(op->ctx->device, (void**)&mg->tail_dev, sizeof(MgTail)) != hipSuccess)
                 rc = fail(TGDK_E_NOMEM, "multigrid tail allocation failed");
             else if (hipMemcpy(mg->tail_dev, &P, sizeof(MgTail), hipMemcpyHostToDevice) != hipSuccess)
                 rc = fail(TGDK_E_HIP, "multigrid tail upload failed");

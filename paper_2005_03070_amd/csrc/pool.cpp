@@ -1,0 +1,97 @@
+// Device memory kept between calls (pool.h).
+#include "pool.h"
+
+#include <algorithm>
+
+namespace tgdk {
+
+// one lock for all pools, so that an allocation can empty every one of a device
+static std::mutex pools_mutex;
+static std::vector<DevPool*> pools;
+
+DevPool::DevPool(int dev) : device(dev) {
+    std::lock_guard<std::mutex> lock(pools_mutex);
+    pools.push_back(this);
+}
+
+DevPool::~DevPool() {
+    std::lock_guard<std::mutex> lock(pools_mutex);
+    pools.erase(std::remove(pools.begin(), pools.end(), this), pools.end());
+    flush();
+}
+
+void DevPool::trim(size_t room) {
+    for (size_t i = 0; i < idle.size();) {  // oldest first
+        if (now - idle[i].stamp <= POOL_AGE && held + room <= POOL_BYTES) {
+            ++i;
+            continue;
+        }
+        held -= idle[i].bytes;
+        (void)hipFree(idle[i].p);
+        idle.erase(idle.begin() + i);
+    }
+}
+
+void DevPool::flush() {
+    for (const Block& b : idle) (void)hipFree(b.p);
+    idle.clear();
+    held = 0;
+}
+
+hipError_t dev_malloc(int device, void** p, size_t bytes) {
+    hipError_t e = hipMalloc(p, bytes);
+    if (e == hipSuccess) return e;
+    (void)hipGetLastError();
+    std::lock_guard<std::mutex> lock(pools_mutex);
+    for (DevPool* pool : pools)
+        if (pool->device == device) pool->flush();
+    e = hipMalloc(p, bytes);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        *p = nullptr;
+    }
+    return e;
+}
+
+void* DevPool::get(size_t bytes) {
+    {
+        std::lock_guard<std::mutex> lock(pools_mutex);
+        ++now;
+        size_t best = idle.size();
+        for (size_t i = 0; i < idle.size(); ++i)
+            if (idle[i].bytes >= bytes && idle[i].bytes - bytes <= idle[i].bytes / 8 &&
+                (best == idle.size() || idle[i].bytes < idle[best].bytes))
+                best = i;
+        if (best < idle.size()) {
+            void* p = idle[best].p;
+            taken[p] = idle[best].bytes;
+            held -= idle[best].bytes;
+            idle.erase(idle.begin() + best);
+            trim(0);
+            return p;
+        }
+        trim(0);
+    }
+    void* p = nullptr;
+    if (dev_malloc(device, &p, bytes) != hipSuccess) return nullptr;
+    std::lock_guard<std::mutex> lock(pools_mutex);
+    taken[p] = bytes;
+    return p;
+}
+
+void DevPool::put(void* p) {
+    if (!p) return;
+    std::lock_guard<std::mutex> lock(pools_mutex);
+    const auto it = taken.find(p);
+    const size_t bytes = it == taken.end() ? POOL_BYTES + 1 : it->second;
+    if (it != taken.end()) taken.erase(it);
+    if (bytes > POOL_BYTES) {
+        (void)hipFree(p);
+        return;
+    }
+    trim(bytes);
+    idle.push_back({p, bytes, now});
+    held += bytes;
+}
+
+}  // namespace tgdk

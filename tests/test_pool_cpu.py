@@ -1,0 +1,117 @@
+"""Memory kept between calls (csrc/pool.cpp) against a stand-in for the driver
+that counts blocks and has a capacity."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2005_03070_amd", "csrc")
+
+DRIVER = r"""
+#include <cstdio>
+#include <cstdlib>
+#include <memory>
+#include <new>
+#include <unordered_map>
+#include "pool.h"
+
+static size_t capacity = (size_t)8 << 30, used = 0;
+static std::unordered_map<char*, size_t> blocks;
+static char* next_block = (char*)0x100000000;
+static int wrong_frees = 0;
+// (hip_runtime_api.h also has a hipMalloc template that calls this one)
+extern "C" hipError_t hipMalloc(void** p, size_t n) {
+    if (used + n > capacity) return hipErrorOutOfMemory;
+    *p = next_block;
+    blocks[next_block] = n;
+    next_block += n;
+    used += n;
+    return hipSuccess;
+}
+extern "C" hipError_t hipFree(void* p) {
+    auto it = blocks.find((char*)p);
+    if (it == blocks.end()) {
+        ++wrong_frees;
+        return hipErrorInvalidValue;
+    }
+    used -= it->second;
+    blocks.erase(it);
+    return hipSuccess;
+}
+extern "C" hipError_t hipGetLastError() { return hipSuccess; }
+
+using namespace tgdk;
+static const size_t MiB = (size_t)1 << 20;
+#define CHECK(c)                                          \
+    do {                                                  \
+        if (!(c)) {                                       \
+            printf("line %d: %s\n", __LINE__, #c);        \
+            exit(1);                                      \
+        }                                                 \
+    } while (0)
+static void keep(DevPool& p, size_t bytes) { p.put(p.get(bytes)); }
+
+int main() {
+    BODY
+    CHECK(wrong_frees == 0);
+    printf("ok\n");
+    return 0;
+}
+"""
+
+
+def _run(tmp_path, body):
+    src, exe = tmp_path / "pool_test.cpp", tmp_path / "pool_test"
+    src.write_text(DRIVER.replace("BODY", body))
+    subprocess.run(["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I", "/opt/rocm/include", "-I", CSRC,
+                    str(src), os.path.join(CSRC, "pool.cpp"), "-o", str(exe), "-lpthread"], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0 and r.stdout.strip() == "ok", r.stdout
+
+
+def test_a_failing_allocation_gets_what_is_held_free(tmp_path):
+    """Every allocation of the library goes through dev_malloc: one that does
+    not fit beside the blocks that pools of its device hold free takes theirs;
+    another device's stay, and so do blocks in use."""
+    _run(tmp_path, r"""
+    capacity = 3000 * MiB;
+    DevPool a(0), b(0), other(1);
+    void* in_use = a.get(100 * MiB);
+    keep(a, 600 * MiB);
+    keep(b, 700 * MiB);
+    keep(other, 800 * MiB);
+    CHECK(used == 2200 * MiB);
+    void* p = nullptr;
+    CHECK(dev_malloc(0, &p, 1500 * MiB) == hipSuccess && p);
+    CHECK(used == 2400 * MiB && blocks.size() == 3);  // in_use, the other device's, p
+    CHECK(blocks.count((char*)in_use) == 1);
+    void* q = p;
+    CHECK(dev_malloc(0, &q, 5000 * MiB) == hipErrorOutOfMemory && !q);
+    CHECK(a.get(5000 * MiB) == nullptr);
+    hipFree(p);
+    a.put(in_use);
+    """)
+
+
+def test_blocks_are_reused_bounded_and_age(tmp_path):
+    _run(tmp_path, r"""
+    capacity = (size_t)64 << 30;
+    {
+        DevPool a(0);
+        void* p = a.get(800 * MiB);
+        a.put(p);
+        CHECK(a.get(700 * MiB) == p);             // an eighth less fits
+        a.put(p);
+        void* q = a.get(699 * MiB);               // less does not
+        CHECK(q != p);
+        a.put(q);
+        keep(a, 900 * MiB);
+        CHECK(used <= POOL_BYTES);
+        keep(a, 3000 * MiB);                      // more than the bound goes back at once
+        CHECK(used <= POOL_BYTES);
+        for (unsigned i = 0; i < 2 * POOL_AGE; ++i) keep(a, 1 * MiB);
+        CHECK(used <= 2 * MiB);
+    }
+    CHECK(used == 0);
+    """)
