@@ -83,6 +83,13 @@ int tgdk_ctx_create(tgdk_ctx* out, int device, void* hip_stream);
 int tgdk_ctx_destroy(tgdk_ctx ctx);
 /* Number of compute units of the context's device (for launch sizing). */
 int tgdk_ctx_num_cus(tgdk_ctx ctx);
+/* Deflation spaces and the workspaces of the calls that build and use them are
+ * kept for the context's later calls when they are given up: all contexts of a
+ * device together keep at most 2 GiB free, blocks that 64 requests did not want
+ * and, where an allocation of this library fails, all of them go back to the
+ * driver.  tgdk_ctx_trim hands back what this context keeps free now (for other
+ * allocators of the process). */
+int tgdk_ctx_trim(tgdk_ctx ctx);
 /* 2-D systems of up to one tile per compute unit (BiCGStab; IDR(s) with s <= 8
  * and no preconditioner; the Arnoldi steps of GMRES and the coarse set-up) are
  * solved by launches that hold up to every compute unit until the solve (the

@@ -7,11 +7,11 @@ include/tgdk.h) with a thin Python binding.
 from . import _lib
 from .api import (DeflationSpace, Multigrid, Operator, Report, SetupReport, coarse_setup, context, defl_from_basis,
                   defl_prolongate, grad_k, one_launch, prolongate, restrict, solve, solve_idr, solve_instances,
-                  solve_noalloc, stream_probe)
+                  solve_noalloc, stream_probe, trim_memory)
 from .autograd import DeflatedSolve, TwoGridSolver
 
 __all__ = ["Operator", "DeflationSpace", "Multigrid", "Report", "SetupReport", "coarse_setup", "context", "defl_from_basis",
            "defl_prolongate", "grad_k", "one_launch", "prolongate", "restrict", "solve", "solve_idr", "solve_instances", "solve_noalloc",
-           "stream_probe",
+           "stream_probe", "trim_memory",
            "DeflatedSolve",
            "TwoGridSolver"]

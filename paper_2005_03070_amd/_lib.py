@@ -90,6 +90,7 @@ SIGNATURES = [
     ("tgdk_ctx_create", I, [PP, I, P]),
     ("tgdk_ctx_destroy", I, [P]),
     ("tgdk_ctx_num_cus", I, [P]),
+    ("tgdk_ctx_trim", I, [P]),
     ("tgdk_ctx_one_launch", I, [P, I]),
     ("tgdk_ctx_time_kernel", I, [P, I]),
     ("tgdk_ctx_kernel_time", I, [P, I, DP, C.POINTER(C.c_longlong)]),

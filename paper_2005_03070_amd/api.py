@@ -32,6 +32,15 @@ def context(device=None):
     return _CTX[key]
 
 
+def trim_memory(device=None):
+    """Hands the memory that the device's contexts keep free for later calls (up
+    to 2 GiB) back to the driver (include/tgdk.h, tgdk_ctx_trim)."""
+    dev = context(device)[1]
+    for h, d in list(_CTX.values()):
+        if d == dev:
+            check(lib().tgdk_ctx_trim(h))
+
+
 def one_launch(mode, device=None):
     """How the current stream's context solves 2-D systems that fit the chip:
     True (the default) in launches that hold it until they end, False in one

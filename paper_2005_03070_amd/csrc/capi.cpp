@@ -368,6 +368,13 @@ int tgdk_ctx_destroy(tgdk_ctx c) {
 
 int tgdk_ctx_num_cus(tgdk_ctx c) { return c ? c->num_cus : 0; }
 
+int tgdk_ctx_trim(tgdk_ctx c) {
+    if (!c) return fail(TGDK_E_INVALID, "bad argument");
+    TGDK_HIP(hipSetDevice(c->device));
+    c->pool.flush();
+    return TGDK_OK;
+}
+
 int tgdk_ctx_one_launch(tgdk_ctx c, int mode) {
     if (!c || mode < TGDK_ONE_LAUNCH_OFF || mode > TGDK_ONE_LAUNCH_CLOSED) return fail(TGDK_E_INVALID, "bad argument");
     c->one_launch = mode;

@@ -8,6 +8,7 @@ namespace tgdk {
 // one lock for all pools, so that an allocation can empty every one of a device
 static std::mutex pools_mutex;
 static std::vector<DevPool*> pools;
+static unsigned long long puts = 0;
 
 DevPool::DevPool(int dev) : device(dev) {
     std::lock_guard<std::mutex> lock(pools_mutex);
@@ -17,25 +18,37 @@ DevPool::DevPool(int dev) : device(dev) {
 DevPool::~DevPool() {
     std::lock_guard<std::mutex> lock(pools_mutex);
     pools.erase(std::remove(pools.begin(), pools.end(), this), pools.end());
-    flush();
+    drop_all();
+}
+
+void DevPool::drop(size_t i) {
+    held -= idle[i].bytes;
+    (void)hipFree(idle[i].p);
+    idle.erase(idle.begin() + i);
+}
+
+void DevPool::drop_all() {
+    while (!idle.empty()) drop(idle.size() - 1);
 }
 
 void DevPool::trim(size_t room) {
-    for (size_t i = 0; i < idle.size();) {  // oldest first
-        if (now - idle[i].stamp <= POOL_AGE && held + room <= POOL_BYTES) {
-            ++i;
-            continue;
+    while (!idle.empty() && now - idle[0].stamp > POOL_AGE) drop(0);  // (in the order of their put)
+    for (;;) {
+        size_t sum = room;
+        DevPool* oldest = nullptr;
+        for (DevPool* p : pools) {
+            if (p->device != device || p->idle.empty()) continue;
+            sum += p->held;
+            if (!oldest || p->idle[0].order < oldest->idle[0].order) oldest = p;
         }
-        held -= idle[i].bytes;
-        (void)hipFree(idle[i].p);
-        idle.erase(idle.begin() + i);
+        if (sum <= POOL_BYTES || !oldest) return;
+        oldest->drop(0);
     }
 }
 
 void DevPool::flush() {
-    for (const Block& b : idle) (void)hipFree(b.p);
-    idle.clear();
-    held = 0;
+    std::lock_guard<std::mutex> lock(pools_mutex);
+    drop_all();
 }
 
 hipError_t dev_malloc(int device, void** p, size_t bytes) {
@@ -44,7 +57,7 @@ hipError_t dev_malloc(int device, void** p, size_t bytes) {
     (void)hipGetLastError();
     std::lock_guard<std::mutex> lock(pools_mutex);
     for (DevPool* pool : pools)
-        if (pool->device == device) pool->flush();
+        if (pool->device == device) pool->drop_all();
     e = hipMalloc(p, bytes);
     if (e != hipSuccess) {
         (void)hipGetLastError();
@@ -90,7 +103,7 @@ void DevPool::put(void* p) {
         return;
     }
     trim(bytes);
-    idle.push_back({p, bytes, now});
+    idle.push_back({p, bytes, now, ++puts});
     held += bytes;
 }
 

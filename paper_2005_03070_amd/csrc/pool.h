@@ -16,9 +16,11 @@ namespace tgdk {
 // 30 vectors to 1023^2 takes 2.8 ms the first times and 21 ms from then on
 // (2.3 GB a call handed back and cleared).
 //
-// A block is reused for requests of its size or up to an eighth less.  At most
-// POOL_BYTES are held free, and a block that no one took for POOL_AGE requests
-// goes back to the driver.  The pool belongs to a context, hence to one stream:
+// A block is reused for requests of its size or up to an eighth less.  All
+// contexts of a device together hold at most POOL_BYTES free (the oldest goes
+// first, whoever's it is), a block that no one took for POOL_AGE requests goes
+// back to the driver, and so does everything free on flush() and when an
+// allocation fails.  The pool belongs to a context, hence to one stream:
 // whatever still uses a block's old contents is ordered before its next use.
 // Handles may be destroyed from any thread (a garbage collector's), so the
 // pools have a lock.
@@ -32,16 +34,18 @@ public:
     DevPool& operator=(const DevPool&) = delete;
     void* get(size_t bytes);  // null: no memory
     void put(void* p);
+    void flush();  // hands back what is free
 
 private:
     friend hipError_t dev_malloc(int device, void** p, size_t bytes);
     struct Block {
         void* p;
         size_t bytes;
-        unsigned long long stamp;
+        unsigned long long stamp, order;  // of put(): this pool's requests, the process's
     };
-    void trim(size_t room);  // hands back old blocks, and the oldest until `room` more bytes fit
-    void flush();
+    void drop(size_t i);
+    void drop_all();
+    void trim(size_t room);  // hands back old blocks, and the device's oldest until `room` more bytes fit
     const int device;
     std::vector<Block> idle;
     std::unordered_map<void*, size_t> taken;

@@ -115,3 +115,28 @@ def test_blocks_are_reused_bounded_and_age(tmp_path):
     }
     CHECK(used == 0);
     """)
+
+
+def test_the_contexts_of_a_device_share_one_bound(tmp_path):
+    """Eight pools of one device and one of another: together the eight hold at
+    most the bound, the block that waits longest goes first, and flush() hands
+    back one pool's."""
+    _run(tmp_path, r"""
+    capacity = (size_t)64 << 30;
+    std::unique_ptr<DevPool> p[8];
+    for (auto& q : p) q.reset(new DevPool(0));
+    DevPool other(1);
+    keep(other, 1024 * MiB);
+    void* first = p[0]->get(512 * MiB);
+    p[0]->put(first);
+    for (int i = 1; i < 8; ++i) keep(*p[i], 512 * MiB);
+    CHECK(used == POOL_BYTES + 1024 * MiB);
+    CHECK(blocks.count((char*)first) == 0);
+    void* last = p[7]->get(512 * MiB);
+    CHECK(used == POOL_BYTES + 1024 * MiB);   // (it had stayed)
+    p[7]->put(last);
+    p[6]->flush();
+    CHECK(used == POOL_BYTES + 512 * MiB);
+    p[7].reset();
+    CHECK(used == POOL_BYTES);
+    """)
