@@ -2,6 +2,7 @@
 #include "pool.h"
 
 #include <algorithm>
+#include <new>
 
 namespace tgdk {
 
@@ -66,7 +67,16 @@ hipError_t dev_malloc(int device, void** p, size_t bytes) {
     return e;
 }
 
-void* DevPool::get(size_t bytes) {
+static bool record(std::unordered_map<void*, size_t>& taken, void* p, size_t bytes) {
+    try {
+        taken[p] = bytes;
+        return true;
+    } catch (const std::bad_alloc&) {
+        return false;
+    }
+}
+
+void* DevPool::get(size_t bytes) noexcept {
     {
         std::lock_guard<std::mutex> lock(pools_mutex);
         ++now;
@@ -77,7 +87,7 @@ void* DevPool::get(size_t bytes) {
                 best = i;
         if (best < idle.size()) {
             void* p = idle[best].p;
-            taken[p] = idle[best].bytes;
+            if (!record(taken, p, idle[best].bytes)) return nullptr;
             held -= idle[best].bytes;
             idle.erase(idle.begin() + best);
             trim(0);
@@ -88,11 +98,12 @@ void* DevPool::get(size_t bytes) {
     void* p = nullptr;
     if (dev_malloc(device, &p, bytes) != hipSuccess) return nullptr;
     std::lock_guard<std::mutex> lock(pools_mutex);
-    taken[p] = bytes;
-    return p;
+    if (record(taken, p, bytes)) return p;
+    (void)hipFree(p);
+    return nullptr;
 }
 
-void DevPool::put(void* p) {
+void DevPool::put(void* p) noexcept {
     if (!p) return;
     std::lock_guard<std::mutex> lock(pools_mutex);
     const auto it = taken.find(p);
@@ -103,7 +114,12 @@ void DevPool::put(void* p) {
         return;
     }
     trim(bytes);
-    idle.push_back({p, bytes, now, ++puts});
+    try {
+        idle.push_back({p, bytes, now, ++puts});
+    } catch (const std::bad_alloc&) {
+        (void)hipFree(p);
+        return;
+    }
     held += bytes;
 }
 

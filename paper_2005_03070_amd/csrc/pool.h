@@ -32,8 +32,11 @@ public:
     ~DevPool();
     DevPool(const DevPool&) = delete;
     DevPool& operator=(const DevPool&) = delete;
-    void* get(size_t bytes);  // null: no memory
-    void put(void* p);
+    // Both are called from C entry points and throw nothing: where there is no
+    // host memory for its record, a block is not handed out (null, as without
+    // device memory), or goes back to the driver.
+    void* get(size_t bytes) noexcept;
+    void put(void* p) noexcept;
     void flush();  // hands back what is free
 
 private:

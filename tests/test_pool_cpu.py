@@ -41,6 +41,16 @@ extern "C" hipError_t hipFree(void* p) {
 }
 extern "C" hipError_t hipGetLastError() { return hipSuccess; }
 
+// host memory that runs out on request
+static bool no_host_memory = false;
+void* operator new(size_t n) {
+    void* p = no_host_memory ? nullptr : malloc(n ? n : 1);
+    if (!p) throw std::bad_alloc();
+    return p;
+}
+void operator delete(void* p) noexcept { free(p); }
+void operator delete(void* p, size_t) noexcept { free(p); }
+
 using namespace tgdk;
 static const size_t MiB = (size_t)1 << 20;
 #define CHECK(c)                                          \
@@ -139,4 +149,27 @@ def test_the_contexts_of_a_device_share_one_bound(tmp_path):
     CHECK(used == POOL_BYTES + 512 * MiB);
     p[7].reset();
     CHECK(used == POOL_BYTES);
+    """)
+
+
+def test_without_host_memory_blocks_go_back_and_nothing_is_thrown(tmp_path):
+    """get() and put() are called from C entry points (also from a garbage
+    collector's thread): with no host memory for a block's record they return
+    null and hand the block back."""
+    _run(tmp_path, r"""
+    DevPool a(0);
+    void* p[3];
+    for (void*& q : p) q = a.get(10 * MiB);
+    a.put(p[0]);
+    blocks.reserve(64);                   // (the stand-in's own table)
+    const size_t before = used;
+    no_host_memory = true;
+    CHECK(a.get(10 * MiB) == nullptr);    // the kept block cannot be recorded as taken
+    a.put(p[1]);
+    a.put(p[2]);
+    no_host_memory = false;
+    CHECK(used <= before);
+    for (int i = 0; i < 8; ++i) keep(a, 10 * MiB);
+    CHECK(used == 10 * MiB || used == 20 * MiB || used == 30 * MiB);
+    CHECK(a.get(10 * MiB) != nullptr);
     """)
