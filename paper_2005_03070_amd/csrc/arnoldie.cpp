@@ -212,7 +212,7 @@ extern "C" int tgdk_defl_improve(tgdk_defl in, const tgdk_arnoldie_params* prm, 
     double* dsc = p;  // [0]: ||z||^2 before, [1]: ||z|| after
     auto done = [&](int code) {
         (void)hipStreamSynchronize(s);
-        ctx->pool.put(base);
+        ctx->pool->put(base);
         return code;
     };
     // the partial sums of both the Gram-Schmidt and the 64 x 64 Gram kernels,
@@ -307,7 +307,7 @@ extern "C" int tgdk_defl_improve(tgdk_defl in, const tgdk_arnoldie_params* prm, 
         return done(fail(TGDK_E_NOMEM, "Arnoldi-E output allocation failed"));
     TGDK_HIP(hipMemcpyAsync(V64, w.Y, sizeof(double) * vec * kk, hipMemcpyDeviceToDevice, s));
     if ((rc = cholqr2(ctx, V64, n, kk)) || (rc = defl_finish(op, tr, V64, kk, store_dtype, out, TGDK_PROJ_GALERKIN))) {
-        ctx->pool.put(V64);
+        ctx->pool->put(V64);
         return done(rc);
     }
     if (rep) {

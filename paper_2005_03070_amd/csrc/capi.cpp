@@ -88,7 +88,7 @@ int ArnoldiSteps::wait(bool* missed) {
 }
 
 void ArnoldiSteps::release() {
-    if (block_) ctx_->pool.put(block_);
+    if (block_) ctx_->pool->put(block_);
     block_ = nullptr;
 }
 
@@ -186,9 +186,9 @@ int cholqr2(tgdk_ctx ctx, double* W, long long n, int k) {
         launch_vmul(in, n, k, dY, k, out, n, n, s);
     }
     if (hipStreamSynchronize(s) != hipSuccess && rc == TGDK_OK) rc = fail(TGDK_E_HIP, "cholqr2 failed");
-    ctx->pool.put(tmp);
-    ctx->pool.put(dY);
-    ctx->pool.put(dG);
+    ctx->pool->put(tmp);
+    ctx->pool->put(dY);
+    ctx->pool->put(dG);
     return rc;
 }
 
@@ -216,9 +216,9 @@ static int defl_factor(tgdk_defl d, const char* singular_msg) {
         hipMemcpyAsync(d->d_hinv, hinv.data(), (size_t)k * k * sizeof(double), hipMemcpyHostToDevice, s) !=
             hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess) {
-        ctx->pool.put(d->d_lu);
-        ctx->pool.put(d->d_piv);
-        ctx->pool.put(d->d_hinv);
+        ctx->pool->put(d->d_lu);
+        ctx->pool->put(d->d_piv);
+        ctx->pool->put(d->d_hinv);
         d->d_lu = d->d_hinv = nullptr;
         d->d_piv = nullptr;
         return rc ? rc : fail(TGDK_E_HIP, "upload of LU failed");
@@ -239,7 +239,7 @@ int defl_finish(tgdk_op op, int transpose, double* V64, int k, int store, tgdk_d
         launch_to_f64(V32, V64, (long long)n * k, s);  // H is formed from the rounded basis
     }
     if ((rc = pool_alloc(ctx, &AV, (size_t)n * k))) {
-        if (V32) ctx->pool.put(V32);
+        if (V32) ctx->pool->put(V32);
         return rc;
     }
     rc = op_apply_internal(op, transpose, TGDK_F64, V64, AV, k);
@@ -263,21 +263,20 @@ int defl_finish(tgdk_op op, int transpose, double* V64, int k, int store, tgdk_d
             hipStreamSynchronize(s) != hipSuccess)
             rc = fail(TGDK_E_HIP, "forming H failed");
     }
-    if (dG) ctx->pool.put(dG);
+    if (dG) ctx->pool->put(dG);
     void* W = nullptr;  // the stored left basis (MinRes only)
     if (minres && !rc) {
         W = store == TGDK_F32 ? (void*)W32 : (void*)AV;
-        if (store == TGDK_F32) ctx->pool.put(AV);
+        if (store == TGDK_F32) ctx->pool->put(AV);
     } else {
-        ctx->pool.put(AV);
-        if (W32) ctx->pool.put(W32);
+        ctx->pool->put(AV);
+        if (W32) ctx->pool->put(W32);
     }
     if (rc) {
-        if (V32) ctx->pool.put(V32);
+        if (V32) ctx->pool->put(V32);
         return rc;
     }
-    tgdk_defl d = new tgdk_defl_s();
-    d->ctx = ctx;
+    tgdk_defl d = new tgdk_defl_s(ctx);
     d->op = op;
     d->transpose = transpose;
     d->k = k;
@@ -289,14 +288,14 @@ int defl_finish(tgdk_op op, int transpose, double* V64, int k, int store, tgdk_d
     d->mvp_build = k;
     if ((rc = defl_factor(d, minres ? "projection matrix H = (AV)^T AV is singular"
                                     : "projection matrix H = V^T A V is singular"))) {
-        if (V32) ctx->pool.put(V32);
-        if (W) ctx->pool.put(W);
+        if (V32) ctx->pool->put(V32);
+        if (W) ctx->pool->put(W);
         delete d;
         return rc;
     }
     if (store == TGDK_F32) {
         d->V = V32;
-        ctx->pool.put(V64);
+        ctx->pool->put(V64);
     } else {
         d->V = V64;
     }
@@ -362,6 +361,7 @@ int tgdk_ctx_destroy(tgdk_ctx c) {
     if (c->mirror) (void)hipHostFree(c->mirror);
     for (auto e : c->events) (void)hipEventDestroy(e);
     for (auto e : c->tevents) (void)hipEventDestroy(e);
+    c->pool->close();
     delete c;
     return TGDK_OK;
 }
@@ -371,7 +371,7 @@ int tgdk_ctx_num_cus(tgdk_ctx c) { return c ? c->num_cus : 0; }
 int tgdk_ctx_trim(tgdk_ctx c) {
     if (!c) return fail(TGDK_E_INVALID, "bad argument");
     TGDK_HIP(hipSetDevice(c->device));
-    c->pool.flush();
+    c->pool->flush();
     return TGDK_OK;
 }
 
@@ -595,11 +595,11 @@ int tgdk_defl_prolongate(tgdk_defl cs, tgdk_op fine, int store_dtype, tgdk_defl*
     launch_prolong(fine->dim, c->n[0], c->n[1], fine->dim == 3 ? c->n[2] : 1, (const double*)cs->V, PW, k,
                    fine->ctx->stream);
     if ((rc = cholqr2(fine->ctx, PW, fine->N, k))) {
-        fine->ctx->pool.put(PW);
+        fine->ctx->pool->put(PW);
         return rc;
     }
     rc = defl_finish(fine, cs->transpose, PW, k, store_dtype, out, TGDK_PROJ_GALERKIN);
-    if (rc) fine->ctx->pool.put(PW);
+    if (rc) fine->ctx->pool->put(PW);
     return rc;
 }
 
@@ -612,11 +612,11 @@ int tgdk_defl_from_basis(tgdk_op op, const double* W, int k, int transpose, int 
     if (rc) return rc;
     TGDK_HIP(hipMemcpyAsync(V, W, (size_t)op->N * k * sizeof(double), hipMemcpyDeviceToDevice, op->ctx->stream));
     if ((rc = cholqr2(op->ctx, V, op->N, k))) {
-        op->ctx->pool.put(V);
+        op->ctx->pool->put(V);
         return rc;
     }
     rc = defl_finish(op, transpose ? 1 : 0, V, k, store_dtype, out, TGDK_PROJ_GALERKIN);
-    if (rc) op->ctx->pool.put(V);
+    if (rc) op->ctx->pool->put(V);
     return rc;
 }
 
@@ -633,7 +633,7 @@ int tgdk_defl_minres(tgdk_defl g, tgdk_defl* out) {
     else
         launch_to_f64((const float*)g->V, V, (long long)g->n * g->k, g->ctx->stream);
     rc = defl_finish(g->op, g->transpose, V, g->k, g->store, out, TGDK_PROJ_MINRES);
-    if (rc) g->ctx->pool.put(V);
+    if (rc) g->ctx->pool->put(V);
     return rc;
 }
 
@@ -651,10 +651,10 @@ int tgdk_defl_precond(tgdk_defl g, tgdk_precond_fn fn, void* user, tgdk_defl* ou
     double *V = nullptr, *Z = nullptr, *AZ = nullptr, *dG = nullptr;
     int rc;
     auto release = [&]() {
-        if (V) ctx->pool.put(V);
-        if (Z) ctx->pool.put(Z);
-        if (AZ) ctx->pool.put(AZ);
-        if (dG) ctx->pool.put(dG);
+        if (V) ctx->pool->put(V);
+        if (Z) ctx->pool->put(Z);
+        if (AZ) ctx->pool->put(AZ);
+        if (dG) ctx->pool->put(dG);
     };
     if ((rc = pool_alloc(ctx, &V, (size_t)n * k)) || (rc = pool_alloc(ctx, &Z, (size_t)n * k)) ||
         (rc = pool_alloc(ctx, &AZ, (size_t)n * k)) || (rc = pool_alloc(ctx, &dG, (size_t)k * k))) {
@@ -675,11 +675,10 @@ int tgdk_defl_precond(tgdk_defl g, tgdk_precond_fn fn, void* user, tgdk_defl* ou
         release();
         return fail(TGDK_E_HIP, "forming H failed");
     }
-    ctx->pool.put(AZ);
-    ctx->pool.put(dG);
+    ctx->pool->put(AZ);
+    ctx->pool->put(dG);
     AZ = dG = nullptr;
-    tgdk_defl d = new tgdk_defl_s();
-    d->ctx = ctx;
+    tgdk_defl d = new tgdk_defl_s(ctx);
     d->op = g->op;
     d->transpose = g->transpose;
     d->k = k;
@@ -725,12 +724,12 @@ int tgdk_defl_copy(tgdk_defl d, double* V_out, double* H_out) {
 
 int tgdk_defl_destroy(tgdk_defl d) {
     if (!d) return TGDK_OK;
-    (void)hipSetDevice(d->ctx->device);
-    d->ctx->pool.put(d->V);
-    d->ctx->pool.put(d->W);
-    d->ctx->pool.put(d->d_lu);
-    d->ctx->pool.put(d->d_piv);
-    d->ctx->pool.put(d->d_hinv);
+    (void)hipSetDevice(d->device);
+    d->pool->put(d->V);
+    d->pool->put(d->W);
+    d->pool->put(d->d_lu);
+    d->pool->put(d->d_piv);
+    d->pool->put(d->d_hinv);
     delete d;
     return TGDK_OK;
 }

@@ -97,11 +97,11 @@ extern "C" int tgdk_coarse_setup(tgdk_op op, const double* b, double* x, const t
     ArnoldiSteps steps1(ctx);  // a cycle's steps in one launch, where that applies
     auto cleanup = [&]() {
         steps1.release();
-        ctx->pool.put(V);
-        ctx->pool.put(Vt);
-        ctx->pool.put(w);
-        ctx->pool.put(Hd);
-        ctx->pool.put(dP);
+        ctx->pool->put(V);
+        ctx->pool->put(Vt);
+        ctx->pool->put(w);
+        ctx->pool->put(Hd);
+        ctx->pool->put(dP);
     };
     if (pool_alloc(ctx, &V, (size_t)n * (m + 1)) || pool_alloc(ctx, &Vt, (size_t)n * (m + 1)) ||
         pool_alloc(ctx, &w, (size_t)n * (prm->precond ? 2 : 1)) || pool_alloc(ctx, &Hd, 2 * hsz + m + 16) ||
@@ -241,7 +241,7 @@ extern "C" int tgdk_coarse_setup(tgdk_op op, const double* b, double* x, const t
                     for (int i = 0; i <= m; ++i)
                         for (int j = 0; j <= m; ++j)
                             orth = std::max(orth, std::fabs(G[(size_t)i * (m + 1) + j] - (i == j ? 1.0 : 0.0)));
-                    ctx->pool.put(dG);
+                    ctx->pool->put(dG);
                     (void)ctx->partial.ensure((size_t)gs_blocks(n) * (MAXK + 1) * sizeof(double));
                     part = (double*)ctx->partial.p;
                 }
@@ -332,7 +332,7 @@ extern "C" int tgdk_coarse_setup(tgdk_op op, const double* b, double* x, const t
     }
     if (rc) {
         cleanup();
-        ctx->pool.put(W);
+        ctx->pool->put(W);
         return rc;
     }
     // final true residual of the coarse solution: ||A x - b||
@@ -347,7 +347,7 @@ extern "C" int tgdk_coarse_setup(tgdk_op op, const double* b, double* x, const t
     tgdk_defl d = nullptr;
     rc = defl_finish(op, tr, W, kk, TGDK_F64, &d, TGDK_PROJ_GALERKIN);
     if (rc) {
-        ctx->pool.put(W);
+        ctx->pool->put(W);
         return rc;
     }
     *out = d;

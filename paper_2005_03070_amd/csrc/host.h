@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <memory>
 #include <string>
 #include <vector>
 
@@ -37,7 +38,7 @@ struct DevBuf {
 }  // namespace tgdk
 
 struct tgdk_ctx_s {
-    explicit tgdk_ctx_s(int dev) : device(dev), partial(dev), solve_ws(dev), pool(dev) {}
+    explicit tgdk_ctx_s(int dev) : device(dev), partial(dev), solve_ws(dev), pool(std::make_shared<tgdk::DevPool>(dev)) {}
     const int device;
     hipStream_t stream = nullptr;
     int num_cus = 0;
@@ -48,7 +49,7 @@ struct tgdk_ctx_s {
     void* zero = nullptr;      // 4 KiB of zeros, never written
     // solve workspace (grow-only, reused across calls)
     tgdk::DevBuf solve_ws;
-    tgdk::DevPool pool;
+    std::shared_ptr<tgdk::DevPool> pool;  // spaces hold it too: they may outlive the context
     tgdk::Mirror* mirror = nullptr;  // host-mapped
     int mirror_cap = 0;
     int one_launch = TGDK_ONE_LAUNCH_ON;
@@ -79,7 +80,10 @@ struct tgdk_op_s {
 };
 
 struct tgdk_defl_s {
-    tgdk_ctx ctx = nullptr;
+    explicit tgdk_defl_s(tgdk_ctx c) : ctx(c), device(c->device), pool(c->pool) {}
+    tgdk_ctx ctx;
+    const int device;                     // what destroying the space needs of its context,
+    std::shared_ptr<tgdk::DevPool> pool;  // which may be gone by then
     tgdk_op op = nullptr;
     int transpose = 0;
     int k = 0;
@@ -130,7 +134,7 @@ DevOp make_devop(const tgdk_op_s* op, int transpose);
 // Memory from a context's pool; TGDK_E_NOMEM (with *p null) when there is none.
 template <class T>
 int pool_alloc(tgdk_ctx ctx, T** p, size_t count) {
-    *p = (T*)ctx->pool.get((count ? count : 1) * sizeof(T));
+    *p = (T*)ctx->pool->get((count ? count : 1) * sizeof(T));
     return *p ? TGDK_OK : fail(TGDK_E_NOMEM, "device memory allocation failed");
 }
 double op_norm1(tgdk_op op, int transpose);

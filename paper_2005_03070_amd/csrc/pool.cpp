@@ -52,6 +52,12 @@ void DevPool::flush() {
     drop_all();
 }
 
+void DevPool::close() {
+    std::lock_guard<std::mutex> lock(pools_mutex);
+    closed = true;
+    drop_all();
+}
+
 hipError_t dev_malloc(int device, void** p, size_t bytes) {
     hipError_t e = hipMalloc(p, bytes);
     if (e == hipSuccess) return e;
@@ -109,7 +115,7 @@ void DevPool::put(void* p) noexcept {
     const auto it = taken.find(p);
     const size_t bytes = it == taken.end() ? POOL_BYTES + 1 : it->second;
     if (it != taken.end()) taken.erase(it);
-    if (bytes > POOL_BYTES) {
+    if (closed || bytes > POOL_BYTES) {
         (void)hipFree(p);
         return;
     }

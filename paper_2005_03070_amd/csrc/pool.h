@@ -38,6 +38,7 @@ public:
     void* get(size_t bytes) noexcept;
     void put(void* p) noexcept;
     void flush();  // hands back what is free
+    void close();  // the context goes: flush(), and nothing is kept from now on
 
 private:
     friend hipError_t dev_malloc(int device, void** p, size_t bytes);
@@ -53,6 +54,7 @@ private:
     std::vector<Block> idle;
     std::unordered_map<void*, size_t> taken;
     size_t held = 0;
+    bool closed = false;
     unsigned long long now = 0;
 };
 

@@ -835,10 +835,10 @@ static int gmres_single(tgdk_ctx ctx, const ProbSpec& p, const tgdk_solve_params
     const size_t hsz = (size_t)(m + 1) * m;
     const bool pre = prm->precond != nullptr;
     auto release = [&]() {
-        ctx->pool.put(V);
-        ctx->pool.put(w);
-        ctx->pool.put(Hd);
-        ctx->pool.put(dy);
+        ctx->pool->put(V);
+        ctx->pool->put(w);
+        ctx->pool->put(Hd);
+        ctx->pool->put(dy);
     };
     if (pool_alloc(ctx, &V, (size_t)n * (m + 1)) || pool_alloc(ctx, &w, (size_t)n * (pre ? 3 : 1)) ||
         pool_alloc(ctx, &Hd, 2 * hsz + m + 8) || pool_alloc(ctx, &dy, (size_t)m + 1)) {
@@ -968,7 +968,7 @@ static int idr_single(tgdk_ctx ctx, const ProbSpec& p, int s, const double* shad
     IdrState* d_st = (IdrState*)(wk + off_st);
     auto done = [&](int code) {
         (void)hipStreamSynchronize(hs);
-        ctx->pool.put(wk);
+        ctx->pool->put(wk);
         return code;
     };
 #define IDR_HIP(call)                                                                        \

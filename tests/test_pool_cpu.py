@@ -173,3 +173,15 @@ def test_without_host_memory_blocks_go_back_and_nothing_is_thrown(tmp_path):
     CHECK(used == 10 * MiB || used == 20 * MiB || used == 30 * MiB);
     CHECK(a.get(10 * MiB) != nullptr);
     """)
+
+
+def test_a_closed_pool_keeps_nothing(tmp_path):
+    _run(tmp_path, r"""
+    DevPool a(0);
+    void *p = a.get(10 * MiB), *q = a.get(10 * MiB);
+    a.put(p);
+    a.close();
+    CHECK(used == 10 * MiB);
+    a.put(q);
+    CHECK(used == 0);
+    """)
