@@ -253,21 +253,32 @@ __device__ __forceinline__ void st_stream(gptr<T> p, T v) {
 // least the geometric schedule's value for icyc; the smaller one is taken
 // (ties count as criterion 1).  Past ncyc the cycle aims straight at tau.
 // float32 inner cycles are floored at fp32_floor.  Returns the criterion
-// (1, 2, or 3 past ncyc).  The one definition for every solver driver.
-__device__ __forceinline__ int cycle_tolerance(double nu, double nu0, double tau, int icyc, int ncyc, int fp32,
-                                               double fp32_floor, double& rt) {
+// (1, 2, or 3 past ncyc).  The one definition for every solver driver;
+// powers(p1, p2) sets p1 = (tau / nu)^(1 / (ncyc - icyc + 1)) and
+// p2 = (tau / nu0)^(icyc / ncyc).
+template <class Powers>
+__device__ __forceinline__ int cycle_choice(double nu, double nu0, double tau, int icyc, int ncyc, int fp32,
+                                            double fp32_floor, double& rt, Powers powers) {
     int branch;
     if (icyc > ncyc) {
         rt = tau / nu;
         branch = 3;
     } else {
-        const double t1 = pow(tau / nu, 1.0 / (double)(ncyc - icyc + 1));
-        const double t2 = (nu0 / nu) * pow(tau / nu0, (double)icyc / (double)ncyc);
+        double t1, p2;
+        powers(t1, p2);
+        const double t2 = (nu0 / nu) * p2;
         branch = t1 <= t2 ? 1 : 2;
         rt = branch == 1 ? t1 : t2;
     }
     if (fp32 == 1 && rt < fp32_floor) rt = fp32_floor;
     return branch;
+}
+__device__ __forceinline__ int cycle_tolerance(double nu, double nu0, double tau, int icyc, int ncyc, int fp32,
+                                               double fp32_floor, double& rt) {
+    return cycle_choice(nu, nu0, tau, icyc, ncyc, fp32, fp32_floor, rt, [&](double& p1, double& p2) {
+        p1 = pow(tau / nu, 1.0 / (double)(ncyc - icyc + 1));
+        p2 = pow(tau / nu0, (double)icyc / (double)ncyc);
+    });
 }
 
 __device__ __forceinline__ bool inside(const DevOp& op, int gx, int gy, int gz) {

@@ -178,7 +178,7 @@ static void gram_block(const double* A, long long lda, int p, const double* B, l
 }
 
 // G (p x q, row-major) = A^T B in blocks of at most GRAM_MAX x GRAM_MAX (the
-// kernel's tile limit), each block's per-workgroup partials summed into its
+// kernel's tile limit), each block's accumulators (a wave's each) summed into its
 // place in G; the blocks run one after another on the stream and share the
 // partial workspace (gram_blocks(n) * GRAM_MAX^2 doubles suffice).
 void launch_gram(const double* A, long long lda, int p, const double* B, long long ldb, int q, long long n, double* G,

@@ -61,7 +61,7 @@ __device__ __forceinline__ u64* cval_slot(const ResTeam& M, int T, int kmax, int
 // this tile's edge values y published and the ring values (waves 4..7: side
 // wave - 4, position lane) returned in ring.  Wave v handles value v.  A team
 // of one takes its own sums; up to 32 workgroups every one reads all partial
-// sums, beyond (33 to 256) workgroup v T / 8 gathers value v and all read its
+// sums, beyond (33 to 256) workgroup (v mod 8) (T / 8) gathers value v and all read its
 // total; the sums have the same order, hence the same bits, either way.
 // True if the grid aborted.
 constexpr int RES_DIRECT = 32;
@@ -261,7 +261,7 @@ __device__ __forceinline__ void basis_update(ResLds& S, const DevProb& P, const 
 // S.y = H^{-1} S.y (column-major, k <= MAXK): 16 lanes a row, 32 rows at a time,
 // 8 consecutive entries a lane in flight.  (A thread a row walked its k entries 16 at a
 // time, a memory latency for each 16: a boundary at 511^2 with 100 columns
-// 138 us, now 135; with 30, 64.8 and 63.9.)
+// 138 us, now 135; with 30, 64.7 and 64.0; with 10 at 63^2 24.1 and 24.3.)
 __device__ __forceinline__ void hinv_apply(ResLds& S, const double* __restrict__ h, int k) {
     const int t = threadIdx.x, lane = t & 15;
     double* out = S.sh;  // k values, free between exchanges
@@ -288,25 +288,20 @@ __device__ __forceinline__ void hinv_apply(ResLds& S, const double* __restrict__
     __syncthreads();
 }
 
-// Start of an inner cycle (all lanes of wave 0): the tolerance of
-// cycle_tolerance with its two powers taken side by side by even and odd
-// lanes, and fresh scalars.
+// Start of an inner cycle (all lanes of wave 0): its tolerance, the two powers
+// taken side by side by even and odd lanes, and fresh scalars.
 __device__ __forceinline__ void start_cycle(ResLds& S, StepHot& N, const ResInit& in, SolveState* st, bool leader,
                                             double nu, double rho0) {
-    int br;
     double rt;
-    if (N.icyc > in.ncyc) {
-        rt = N.tau / nu;
-        br = 3;
-    } else {
-        const bool odd = threadIdx.x & 1;
-        const double pw = pow(N.tau / (odd ? N.nu0 : nu),
-                              (odd ? (double)N.icyc : 1.0) / (double)(odd ? in.ncyc : in.ncyc - N.icyc + 1));
-        const double t1 = lane_value<0>(pw), t2 = (N.nu0 / nu) * lane_value<1>(pw);
-        br = t1 <= t2 ? 1 : 2;
-        rt = br == 1 ? t1 : t2;
-    }
-    if (in.precision == 1 && rt < in.fp32_floor) rt = in.fp32_floor;
+    const int br = cycle_choice(nu, N.nu0, N.tau, N.icyc, in.ncyc, in.precision, in.fp32_floor, rt,
+                                [&](double& p1, double& p2) {
+                                    const bool odd = threadIdx.x & 1;
+                                    const double pw =
+                                        pow(N.tau / (odd ? N.nu0 : nu), (odd ? (double)N.icyc : 1.0) /
+                                                                            (double)(odd ? in.ncyc : in.ncyc - N.icyc + 1));
+                                    p1 = lane_value<0>(pw);
+                                    p2 = lane_value<1>(pw);
+                                });
     cycle_reset(N, nu, rho0, rt);
     if (leader) {
         S.branch[br] += 1;
