@@ -211,18 +211,32 @@ void launch_coarsen_kcell(int ncx, int ncy, const double* kf, double* kc, hipStr
 // exact up to the single rounding of each two-term sum.
 // A wave takes a fine row: which coarse rows it lies between is decided once,
 // and a lane forms the points 2 I and 2 I + 1 from coarse values I - 1 and I.
-// Bound by the stores: 1023^2 x 30 writes 251 MB in 91 us (one point a thread
-// with its divisions: 180 us).
-__global__ __launch_bounds__(256) void k_prolong(int dim, int ncx, int ncy, int ncz, const double* __restrict__ vc,
-                                                 double* __restrict__ vf) {
+// Rows of at most 32 such pairs share a wave (PROL_NARROW, 1 << lw lanes a row),
+// and where there are too few rows for the chip each is cut into nseg parts of seg
+// pairs (PROL_PARTS).  Bound by the stores: 1023^2 x 30 writes 251 MB in 91 us (one
+// point a thread with its divisions: 180 us).  Eight columns, one point a thread | a
+// wave for every row | this: 7 x 131071 62 | 471 | 43 us, 31 x 32767 70 | 149 | 43,
+// 32767 x 7 24 | 134 | 22, 3 x 3 x 200001 212 | 1900 | 117.
+enum : int { PROL_ROWS, PROL_NARROW, PROL_PARTS };
+template <int MODE>
+__global__ __launch_bounds__(256) void k_prolong(int dim, int ncx, int ncy, int ncz, int lw, int nseg, int seg,
+                                                 const double* __restrict__ vc, double* __restrict__ vf) {
     typedef double pair_t __attribute__((ext_vector_type(2), aligned(8)));
     const int nfx = 2 * ncx + 1, nfy = 2 * ncy + 1, nfz = dim == 3 ? 2 * ncz + 1 : 1;
     const long long nrow = (long long)nfy * nfz, ncn = (long long)ncx * ncy * ncz;
     vc += blockIdx.y * ncn;
     vf += blockIdx.y * nrow * nfx;
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    for (long long rw = blockIdx.x * 4LL + w; rw < nrow; rw += gridDim.x * 4LL) {
-        const int fj = (int)(rw % nfy), fk = (int)(rw / nfy);
+    constexpr bool NARROW = MODE == PROL_NARROW, PARTS = MODE == PROL_PARTS;
+    const int rows = NARROW ? 64 >> lw : 1;  // of a wave
+    const long long units = NARROW ? (nrow + rows - 1) / rows : PARTS ? nrow * nseg : nrow;
+    for (long long u = blockIdx.x * 4LL + w; u < units; u += gridDim.x * 4LL) {
+        const long long rw = NARROW ? u * rows + (lane >> lw) : PARTS ? u / nseg : u;
+        if (NARROW && rw >= nrow) continue;
+        const int i0 = PARTS ? (int)(u - rw * nseg) * seg : 0;
+        // (narrow: fewer than 2^31 rows, a division of 32 bits a lane)
+        const int fk = NARROW ? (int)((unsigned)rw / (unsigned)nfy) : (int)(rw / nfy);
+        const int fj = NARROW ? (int)((unsigned)rw - (unsigned)fk * (unsigned)nfy) : (int)(rw % nfy);
         // coarse rows J0, J1 and planes K0, K1 (the same where the point lies on them)
         const bool jodd = fj & 1, kodd = dim == 2 || (fk & 1);
         const int J1 = fj >> 1, J0 = jodd ? J1 : J1 - 1, K1 = dim == 2 ? 0 : fk >> 1, K0 = kodd ? K1 : K1 - 1;
@@ -236,7 +250,8 @@ __global__ __launch_bounds__(256) void k_prolong(int dim, int ncx, int ncy, int 
             return jodd ? line(I, J1, K) : 0.5 * line(I, J0, K) + 0.5 * line(I, J1, K);
         };
         double* out = vf + rw * nfx;
-        for (int I = lane; I <= ncx; I += 64) {
+        const int end = PARTS && ncx + 1 - i0 > seg ? i0 + seg : ncx + 1;
+        for (int I = i0 + (NARROW ? lane & ((1 << lw) - 1) : lane); I < end; I += NARROW ? 1 << lw : 64) {
             const pair_t v = kodd ? plane(I, K1) : 0.5 * plane(I, K0) + 0.5 * plane(I, K1);
             if (I < ncx)
                 *reinterpret_cast<pair_t*>(out + 2 * I) = v;
@@ -248,8 +263,20 @@ __global__ __launch_bounds__(256) void k_prolong(int dim, int ncx, int ncy, int 
 
 void launch_prolong(int dim, int ncx, int ncy, int ncz, const double* vc, double* vf, int ncols, hipStream_t s) {
     const long long nrow = (long long)(2 * ncy + 1) * (dim == 3 ? 2 * ncz + 1 : 1);
-    const int blocks = (int)((nrow + 3) / 4 < 16384 ? (nrow + 3) / 4 : 16384);
-    hipLaunchKernelGGL(k_prolong, dim3(blocks, ncols), dim3(256), 0, s, dim, ncx, ncy, ncz, vc, vf);
+    int lw = 1, seg = (ncx + 64) / 64 * 64;  // pairs a row has: ncx + 1
+    while ((1 << lw) < ncx + 1 && lw < 6) ++lw;
+    // parts while there are fewer than 2048 waves (eight a compute unit)
+    while (seg > 64 && nrow * ncols * ((ncx + seg) / seg) < 2048) seg = (seg / 2 + 63) / 64 * 64;
+    const int nseg = (ncx + seg) / seg;
+    const int mode = lw < 6 && nrow < (1LL << 31) ? PROL_NARROW : nseg > 1 ? PROL_PARTS : PROL_ROWS;
+    const long long units = mode == PROL_NARROW ? (nrow + (64 >> lw) - 1) / (64 >> lw) : nrow * nseg;
+    const dim3 grid((int)((units + 3) / 4 < 16384 ? (units + 3) / 4 : 16384), ncols);
+    if (mode == PROL_NARROW)
+        hipLaunchKernelGGL(k_prolong<PROL_NARROW>, grid, dim3(256), 0, s, dim, ncx, ncy, ncz, lw, nseg, seg, vc, vf);
+    else if (mode == PROL_PARTS)
+        hipLaunchKernelGGL(k_prolong<PROL_PARTS>, grid, dim3(256), 0, s, dim, ncx, ncy, ncz, lw, nseg, seg, vc, vf);
+    else
+        hipLaunchKernelGGL(k_prolong<PROL_ROWS>, grid, dim3(256), 0, s, dim, ncx, ncy, ncz, lw, nseg, seg, vc, vf);
 }
 
 // Full weighting: 1/4, 1/2, 1/4 along x, then y, then z (added in that order).
