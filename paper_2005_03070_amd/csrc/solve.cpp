@@ -206,18 +206,35 @@ static int tile_count(const tgdk_op op, int rows) {
     return (int)(((op->n[0] + RES_TILE - 1LL) / RES_TILE) * ((op->n[1] + rows - 1LL) / rows));
 }
 
+// Whether one launch is for this BiCGStab system: it fits, and it is not one of the
+// few-tile systems with a large float64 space.  Their boundary streams all columns
+// through one or two compute units (one tile, us: 58, 116 and 298 for 40, 100 and 256
+// columns; step kernel 73, 111 and 247), and with so many vectors a cycle has too few
+// iterations (11.8 us gained each) to make up for it.  ms a solve to 1e-8 with 20 and 50
+// cycles, step kernel | one launch: 63^2 with 100 vectors 2.55 | 2.44 and 3.9 | 4.2, with
+// 200 3.7 | 4.5 and 5.8 | 7.7; 127 x 31 with 200 4.5 | 5.1 and 8.7 | 10.9; 127^2 (four
+// tiles) with 200 6.1 | 5.5 and 10.6 | 10.9.  A float32 basis takes half as long.
+static bool one_launch_for(const ProbSpec& p, int units) {
+    const int tiles = tile_count(p.op, RES_TILE);
+    return tiles <= units && !(tiles <= 2 && p.defl && p.defl->k > 128 && p.defl->store == TGDK_F64);
+}
+
 static int resident_team(tgdk_ctx ctx, const std::vector<ProbSpec>& ps, const tgdk_solve_params* prm, int idr_s) {
     if (ps[0].op->dim != 2 || ctx->one_launch == TGDK_ONE_LAUNCH_OFF) return 0;
+    const int units = std::min(ctx->num_cus, 256);
     int rows = RES_TILE;
     if (prm->method == TGDK_IDRS_PROJ) {
-        rows = prm->precond ? 0 : resident_idr_rows(idr_s, make_devop(ps[0].op, 0), std::min(ctx->num_cus, 256));
+        rows = prm->precond ? 0 : resident_idr_rows(idr_s, make_devop(ps[0].op, 0), units);
         if (rows == 0) return 0;
     } else if (prm->method != TGDK_BICGSTAB_PROJ || ctx->time_which) {
         return 0;
+    } else {
+        for (const auto& p : ps)
+            if (!one_launch_for(p, units)) return 0;
     }
     int team = 0;
     for (const auto& p : ps) team = std::max(team, tile_count(p.op, rows));
-    return team <= std::min(ctx->num_cus, 256) ? team : 0;
+    return team <= units ? team : 0;
 }
 
 static void set_space(DevProb& P, tgdk_defl d) {
@@ -724,9 +741,9 @@ static int bicgstab_group(tgdk_ctx ctx, const std::vector<ProbSpec>& ps, const t
     return rc;
 }
 
-// The systems of a call in groups that are solved one after another: the ones
-// past one tile per compute unit (the step kernel's) are one group, the others
-// are split by tile count where that is faster.  With one size for all teams a
+// The systems of a call in groups that are solved one after another: the step
+// kernel's (one_launch_for) are one group, the others are split by tile count where
+// that is faster.  With one size for all teams a
 // 1023^2 system beside 256 of 127^2 left a single team of 256 workgroups that
 // took them in turn: 490 ms, where the step kernel advances all of them in each
 // launch in 213; in groups 22.  (One 1023^2 and 128 of 63^2: 156, 88 and 15 ms.)
@@ -748,21 +765,21 @@ static int bicgstab_systems(tgdk_ctx ctx, const std::vector<ProbSpec>& ps, const
         }
     const int n = (int)ps.size(), units = std::min(ctx->num_cus, 256);
     std::vector<int> tiles(n), order(n);
-    bool mixed = false;
-    for (int j = 0; j < n; ++j) {
-        tiles[j] = tile_count(ps[j].op, RES_TILE);
-        order[j] = j;
-        mixed = mixed || tiles[j] != tiles[0];
-    }
-    if (!mixed || ps[0].op->dim != 2 || ctx->time_which) return bicgstab_group(ctx, ps, prm, reps, ext);
-    auto side = [&](int j) { return std::max(ps[j].op->n[0], ps[j].op->n[1]); };
-    // 0: more tiles than units; else 1 + ceil(log2(tiles))
+    // 0: the step kernel's; else 1 + ceil(log2(tiles))
     auto size_class = [&](int j) {
-        if (tiles[j] > units) return 0;
+        if (!one_launch_for(ps[j], units)) return 0;
         int c = 0;
         while (tiles[j] > (1 << c)) ++c;
         return c + 1;
     };
+    bool mixed = false;
+    for (int j = 0; j < n; ++j) {
+        tiles[j] = tile_count(ps[j].op, RES_TILE);
+        order[j] = j;
+        mixed = mixed || tiles[j] != tiles[0] || size_class(j) != size_class(0);
+    }
+    if (!mixed || ps[0].op->dim != 2 || ctx->time_which) return bicgstab_group(ctx, ps, prm, reps, ext);
+    auto side = [&](int j) { return std::max(ps[j].op->n[0], ps[j].op->n[1]); };
     constexpr int NCLASS = 10;
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return size_class(a) < size_class(b); });
     std::vector<int> start(NCLASS + 1, n);  // first position of a class

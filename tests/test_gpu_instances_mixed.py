@@ -77,3 +77,27 @@ def test_a_large_system_does_not_slow_the_small_ones():
     parts = best(lambda: tg().solve(ops[0], bs[0], **KW)) + best(
         lambda: tg().solve_instances(ops[1:], [None] * 96, bs[1:], **KW))
     assert whole <= 1.5 * parts
+
+
+@pytest.mark.parametrize("store", [torch.float64, torch.float32])
+def test_spaces_past_what_one_or_two_tiles_take(store):
+    """128 and 129 float64 vectors on one and two tiles (one launch, and the step
+    kernel), 129 on three, alone and in one call: each has the bits of its own
+    call, and of a launch per step exactly where that is chosen."""
+    specs = [((63, 40), 128), ((63, 40), 129), ((64, 64), 129), ((64, 128), 129), ((65, 60), 128), ((64, 129), 129)]
+    ops, bs = _instances([d for d, _ in specs])
+    spaces = [tg().defl_from_basis(o, torch.tensor(W.rng(j).standard_normal((k, o.n)), device=DEV), store=store)
+              for j, (o, (_, k)) in enumerate(zip(ops, specs))]
+    # (three iterations, where the two paths differ in the last bits)
+    kw = dict(rtol=1e-12, ncyc=3, max_extra=0, maxit_cycle=1)
+    xs, reps = tg().solve_instances(ops, spaces, bs, **kw)
+    for o, (d, k), b, sp, x in zip(ops, specs, bs, spaces, xs):
+        assert torch.equal(tg().solve(o, b, defl=sp, **kw)[0], x), (d, k)
+        tg().one_launch(False)
+        try:
+            off = tg().solve(o, b, defl=sp, **kw)[0]
+        finally:
+            tg().one_launch(True)
+        stepped = store == torch.float64 and k > 128 and d != (64, 129)
+        assert torch.equal(off, x) == stepped, (d, k)
+        assert torch.linalg.norm(off - x) <= 1e-10 * torch.linalg.norm(off)
