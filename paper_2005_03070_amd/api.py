@@ -439,7 +439,7 @@ def solve_idr(op, b, s=4, shadow=None, x0=None, defl=None, ncyc=20, precision="f
 
 def solve_instances(ops, defls, bs, x0s=None, ncyc=20, precision="fp64", rtol=1e-8, maxit_cycle=100000,
                     max_extra=None, fp32_floor=1e-4, outs=None):
-    """Independent instances solved together (one launch per step covers all)."""
+    """Independent instances solved together (include/tgdk.h, tgdk_solve_instances)."""
     ni = len(ops)
     if outs is None:
         outs = [torch.empty_like(b) for b in bs]

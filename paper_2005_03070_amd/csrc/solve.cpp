@@ -754,7 +754,7 @@ static int bicgstab_group(tgdk_ctx ctx, const std::vector<ProbSpec>& ps, const t
 // measured for 4, 16, 64 and 256), and a grid needs iterations in proportion to
 // its longer side.  What a system's numbers are does not depend on its group.
 static int bicgstab_systems(tgdk_ctx ctx, const std::vector<ProbSpec>& ps, const tgdk_solve_params* prm,
-                            tgdk_solve_report* reps, const ExtWs* ext = nullptr) {
+                            tgdk_solve_report* reps) {
     const auto t0 = std::chrono::steady_clock::now();
     int vtype = -1;
     for (const auto& p : ps)
@@ -778,7 +778,8 @@ static int bicgstab_systems(tgdk_ctx ctx, const std::vector<ProbSpec>& ps, const
         order[j] = j;
         mixed = mixed || tiles[j] != tiles[0] || size_class(j) != size_class(0);
     }
-    if (!mixed || ps[0].op->dim != 2 || ctx->time_which) return bicgstab_group(ctx, ps, prm, reps, ext);
+    if (!mixed || ps[0].op->dim != 2 || ctx->time_which || ctx->one_launch == TGDK_ONE_LAUNCH_OFF)
+        return bicgstab_group(ctx, ps, prm, reps);
     auto side = [&](int j) { return std::max(ps[j].op->n[0], ps[j].op->n[1]); };
     constexpr int NCLASS = 10;
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return size_class(a) < size_class(b); });
@@ -825,7 +826,7 @@ static int bicgstab_systems(tgdk_ctx ctx, const std::vector<ProbSpec>& ps, const
         std::vector<ProbSpec> gp;
         for (int j : part) gp.push_back(ps[j]);
         std::vector<tgdk_solve_report> gr(part.size());
-        const int grc = bicgstab_group(ctx, gp, prm, gr.data(), ext);
+        const int grc = bicgstab_group(ctx, gp, prm, gr.data());
         if (grc < 0 && grc != TGDK_E_NONFINITE) return grc;
         rc = worst(rc, grc);
         for (size_t i = 0; i < part.size(); ++i) reps[part[i]] = gr[i];
